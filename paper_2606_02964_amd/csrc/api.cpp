@@ -112,6 +112,7 @@ msa_status msa::forward_impl(const char* who, msa_plan_t plan, const void* q, co
     m.num_q_heads = s.num_q_heads;
     m.group = hp.group;
     m.tile_rows = hp.tile_rows;
+    m.max_rows = hp.max_merge_rows;
     rc = msa::launch_merge(m, s.head_dim, (int)hp.merge.size(), hip_stream);
     if (rc != 0) return set_error(MSA_ERR_DEVICE, std::string(w + ": merge launch failed: ") +
                                                       hipGetErrorString((hipError_t)rc));

@@ -903,39 +903,61 @@ __global__ __launch_bounds__(256, 2) void msa_decode_kernel(AttnParams p) {
   }
 }
 
+// msa_merge: one workgroup per (split tile, chunk of kRows rows), D / 4 threads
+// to a row, 4 channels each.  Bound by reading the partials; a tile's rows are
+// spread over workgroups because a plan may split few tiles into many pieces
+// (58 tiles of 128 rows x 29 pieces, d = 128: 212 us with one workgroup per
+// tile, about 16 us in this form; 688 tiles x 2-5 pieces: 71 us and 34 us).
+// The lse and O of kBatch pieces load together, so that up to
+// kBatch pieces cost one memory round trip.
 template <int D>
 __global__ __launch_bounds__(256) void msa_merge_kernel(MergeParams p) {
   constexpr int kThreadsPerRow = D / 4;
-  constexpr int kRowsPerPass = 256 / kThreadsPerRow;
+  constexpr int kRows = 256 / kThreadsPerRow;
+  constexpr int kBatch = 8;
   const MergeItem mi = p.merge[blockIdx.x];
   const int G = p.group;
-  const int rows = mi.nrows * G;
+  const int r = blockIdx.y * kRows + threadIdx.x / kThreadsPerRow;
+  if (r >= mi.nrows * G) return;
   const int sub = threadIdx.x % kThreadsPerRow;
   const int R = p.tile_rows;
   const int64_t slot_f = (int64_t)R * (D + 1);
-  for (int r = threadIdx.x / kThreadsPerRow; r < rows; r += kRowsPerPass) {
-    const int t = r / G, hh = r - t * G;
-    const int tok = mi.row0 + t, head = mi.kv_head * G + hh;
-    float mx = -__builtin_inff();
-    for (int s = 0; s < mi.nsplit; ++s)
-      mx = fmaxf(mx, p.ws[(int64_t)(mi.slot0 + s) * slot_f + (int64_t)R * D + r]);
-    const float mu = mx == -__builtin_inff() ? 0.0f : mx;
-    float L = 0.0f;
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int s = 0; s < mi.nsplit; ++s) {
-      const float* base = p.ws + (int64_t)(mi.slot0 + s) * slot_f;
-      const float wgt = __builtin_amdgcn_exp2f((base[(int64_t)R * D + r] - mu) * kLog2e);
-      L += wgt;
-      const f32x4 os = *reinterpret_cast<const f32x4*>(base + r * D + sub * 4);
-      acc += wgt * os;
-    }
-    const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-    bf16x4 v;
+  const int t = r / G, hh = r - t * G;
+  const int tok = mi.row0 + t, head = mi.kv_head * G + hh;
+  const float* base = p.ws + (int64_t)mi.slot0 * slot_f;
+  float mx = -__builtin_inff(), L = 0.0f;
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int s0 = 0; s0 < mi.nsplit; s0 += kBatch) {
+    float ls[kBatch];
+    f32x4 os[kBatch];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = (__bf16)(acc[j] * inv);
-    *reinterpret_cast<bf16x4*>(p.o + (int64_t)tok * p.o_st + (int64_t)head * p.o_sh + sub * 4) = v;
-    if (p.lse && sub == 0) p.lse[(int64_t)tok * p.num_q_heads + head] = mu + __logf(L);
+    for (int u = 0; u < kBatch; ++u) {
+      const float* slot = base + (int64_t)min(s0 + u, mi.nsplit - 1) * slot_f;
+      ls[u] = slot[(int64_t)R * D + r];
+      os[u] = *reinterpret_cast<const f32x4*>(slot + r * D + sub * 4);
+    }
+    float m_new = mx;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) m_new = fmaxf(m_new, ls[u]);
+    const float mu = m_new == -__builtin_inff() ? 0.0f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f((mx - mu) * kLog2e);  // 0 on the first batch
+    L *= alpha;
+    acc *= alpha;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const float wgt = s0 + u < mi.nsplit ? __builtin_amdgcn_exp2f((ls[u] - mu) * kLog2e) : 0.0f;
+      L += wgt;
+      acc += wgt * os[u];
+    }
+    mx = m_new;
   }
+  const float inv = L > 0.0f ? 1.0f / L : 0.0f;
+  bf16x4 v;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = (__bf16)(acc[j] * inv);
+  *reinterpret_cast<bf16x4*>(p.o + (int64_t)tok * p.o_st + (int64_t)head * p.o_sh + sub * 4) = v;
+  if (p.lse && sub == 0)
+    p.lse[(int64_t)tok * p.num_q_heads + head] = (mx == -__builtin_inff() ? 0.0f : mx) + __logf(L);
 }
 
 // The precise-weights forms are separate instantiations, so that the
@@ -971,10 +993,12 @@ int launch_attn(const AttnParams& p, int head_dim, int tile_rows, int num_wg, vo
 int launch_merge(const MergeParams& p, int head_dim, int num_merge, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (num_merge <= 0) return 0;
+  const int rows_per_wg = 1024 / head_dim;  // kRows of msa_merge_kernel
+  const dim3 grid(num_merge, (p.max_rows + rows_per_wg - 1) / rows_per_wg);
   if (head_dim == 128)
-    hipLaunchKernelGGL(msa_merge_kernel<128>, dim3(num_merge), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(msa_merge_kernel<128>, grid, dim3(256), 0, s, p);
   else if (head_dim == 64)
-    hipLaunchKernelGGL(msa_merge_kernel<64>, dim3(num_merge), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(msa_merge_kernel<64>, grid, dim3(256), 0, s, p);
   else
     return (int)hipErrorInvalidValue;
   return (int)hipGetLastError();

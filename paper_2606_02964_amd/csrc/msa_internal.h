@@ -84,6 +84,7 @@ struct MergeParams {
   int32_t num_q_heads;
   int32_t group;
   int32_t tile_rows;  // rows of a workspace slot
+  int32_t max_rows;   // rows (tokens x G) of the largest split tile
 };
 
 // Launchers (attn.hip).  Return a hipError_t value as int.

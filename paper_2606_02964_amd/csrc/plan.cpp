@@ -319,6 +319,7 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
     }
     P.merge.push_back(MergeItem{u.seq, u.kv_head, u.row0, u.nrows, (int32_t)nsplit, slot0, 0, 0});
     P.max_splits = std::max<int64_t>(P.max_splits, nsplit);
+    P.max_merge_rows = std::max<int32_t>(P.max_merge_rows, u.nrows * G);
   }
   P.num_slots = slots;
   P.workspace_bytes = slots * slot_floats(d, P.tile_rows) * (int64_t)sizeof(float);

@@ -25,6 +25,7 @@ struct HostPlan {
   std::vector<AppendItem> append; // one per (segment, cache block) slice
   int64_t num_tiles = 0;          // tiles x kv heads before splitting
   int64_t max_splits = 1;
+  int32_t max_merge_rows = 0;     // rows (tokens x G) of the largest split tile
   int64_t num_slots = 0;          // workspace partial slots
   int64_t workspace_bytes = 0;
   double useful_flops = 0, tile_flops = 0, planned_bytes = 0, min_bytes = 0;
