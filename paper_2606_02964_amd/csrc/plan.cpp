@@ -18,24 +18,28 @@
 //      than 32 rows (decode-like plans: the four waves of a workgroup then
 //      split the tile's keys);
 //   3. units: tile x KV head, keys [0, max position in tile + 1);
-//   4. key splits: units longer than a third of a workgroup slot's share of
-//      the work are cut into 64-aligned key ranges, merged later by
-//      log-sum-exp; with 32-row tiles the cut length is the shortest whose
-//      pieces all fit one round of the workgroup slots;
-//   5. order: (sequence, KV head) groups are spread over the 8 XCDs (blockIdx
-//      i runs on XCD i % 8) so tiles sharing K/V share one XCD's L2.  Inside
-//      each XCD, groups start in decreasing order of their longest piece and
-//      a group's pieces run back to back, longest first, so that no long
+//   4. key splits of 32-row plans: the cut length is the shortest whose
+//      pieces all fit one round of the workgroup slots; other plans cut
+//      units in step 6.  Split units are merged later by log-sum-exp;
+//   5. order: (sequence, KV head) groups keep to one of the 8 XCDs (blockIdx
+//      i runs on XCD i % 8) so tiles sharing K/V share one XCD's L2; groups
+//      that would leave the XCDs uneven are spread over few of them.  Inside
+//      each XCD, groups start in decreasing order of their longest chunk and
+//      a group's chunks run back to back, longest first, so that no long
 //      piece (a decode row over a long context) is left for the end;
 //   6. workgroups: the launch is persistent, one workgroup per slot, each
 //      with its own list of items; each XCD's queue is dealt out in order to
-//      the least-loaded workgroup of that XCD.
+//      the least-loaded workgroup of that XCD, and a unit that would carry a
+//      workgroup past the mean load is cut there.
 #include "plan.h"
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <numeric>
+#include <queue>
+#include <utility>
 
 namespace msa {
 namespace {
@@ -50,6 +54,19 @@ constexpr int64_t kWideMinTiles = 1024;  // narrow tiles from which wide tiles p
 constexpr double kWideMinStepsPerSlot = 384.0;
 constexpr double kWasteFrac = 0.125;     // masked keys allowed per tile, relative
 constexpr int64_t kMinSplitKeys = 1024;  // never split below this many keys
+constexpr int64_t kMinSplitSteps = kMinSplitKeys / kKvStep;
+constexpr int64_t kMinTailSteps = kMinSplitSteps / 2;  // shortest remainder of a cut unit
+// cost of starting and ending an item, in key steps: 7-9 us against 1.9 us a
+// step (128- and 256-row tiles); small beside a streamed step of a 32-row tile
+constexpr double kItemSteps = 4.0;
+constexpr double kItemStepsDecode = 1.0;
+// an XCD's load over the mean that still counts as even: for a group of more
+// than half an XCD's share, and for a smaller one (spreading it gains less
+// and costs as much L2)
+constexpr double kHomeSlack = 0.03;
+constexpr double kHomeSlackSmall = 0.15;
+constexpr double kOneRoundFactor = 1.1;  // one piece per workgroup preferred up to this times the packed load
+constexpr double kCutSlack = 0.02;       // a workgroup's load over the mean before a unit is cut
 
 msa_status fail(std::string* err, msa_status st, const std::string& msg) {
   *err = msg;
@@ -257,182 +274,268 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
   const int32_t Hkv = s.num_kv_heads, d = s.head_dim;
   P.num_tiles = (int64_t)units.size();
 
-  // 4. key splits
+  // 4. key splits decided by length alone: forced, or those of 32-row plans.
+  // Other plans cut units where the workgroups' loads need it (step 6).
   auto steps = [](int64_t keys) { return (keys + kKvStep - 1) / kKvStep; };
-  int64_t split_keys = 0;  // 0: no split
-  if (o.kv_split_tokens > 0) {
-    split_keys = o.kv_split_tokens;
-  } else if (!(o.flags & MSA_PLAN_NO_AUTO_SPLIT) && !units.empty()) {
-    double total_steps = 0;
-    for (const Unit& u : units) total_steps += (double)(steps(u.kv_hi) + 1);
-    if (P.tile_rows == kTileRowsDecode) {
-      // 32-row tiles (decode-like, bound by K/V streaming; the four waves of
-      // a workgroup already split an item's keys): all pieces in one round
-      // of the workgroup slots, the longest piece as short as possible, i.e.
-      // the shortest 64-aligned piece length whose piece count fits the
-      // slots (no split if the units alone exceed them)
-      auto pieces_at = [&](int64_t len) {
-        int64_t c = 0;
-        for (const Unit& u : units) c += (u.kv_hi + len - 1) / len;
-        return c;
-      };
-      int64_t longest = 0;
-      for (const Unit& u : units) longest = std::max<int64_t>(longest, u.kv_hi);
-      int64_t lo = kKvStep, hi = (longest + kKvStep - 1) / kKvStep * kKvStep;
-      if ((int64_t)units.size() <= slots_total) {
-        while (lo < hi) {  // smallest length with pieces_at(length) <= slots
-          const int64_t mid = (lo / kKvStep + hi / kKvStep) / 2 * kKvStep;
-          if (pieces_at(mid) <= slots_total) hi = mid; else lo = mid + kKvStep;
-        }
-        split_keys = std::max<int64_t>(kMinSplitKeys, lo);
-      }
-    } else {
-      // aim at about 3 work items per workgroup slot: a unit longer than
-      // this share of the total is cut into pieces no longer than the share
-      const int64_t share = (int64_t)std::ceil(total_steps / (3.0 * slots_total)) * kKvStep;
-      split_keys = std::max<int64_t>(kMinSplitKeys, share);
+  const bool auto_split = o.kv_split_tokens == 0 && !(o.flags & MSA_PLAN_NO_AUTO_SPLIT);
+  const bool cut_to_fit = auto_split && P.tile_rows != kTileRowsDecode;
+  int64_t split_keys = o.kv_split_tokens;  // 0: no split
+  if (auto_split && P.tile_rows == kTileRowsDecode && !units.empty() && (int64_t)units.size() <= slots_total) {
+    // 32-row tiles (decode-like, bound by K/V streaming; the four waves of
+    // a workgroup already split an item's keys): all pieces in one round
+    // of the workgroup slots, the longest piece as short as possible, i.e.
+    // the shortest 64-aligned piece length whose piece count fits the
+    // slots (no split if the units alone exceed them)
+    auto pieces_at = [&](int64_t len) {
+      int64_t c = 0;
+      for (const Unit& u : units) c += (u.kv_hi + len - 1) / len;
+      return c;
+    };
+    int64_t longest = 0;
+    for (const Unit& u : units) longest = std::max<int64_t>(longest, u.kv_hi);
+    int64_t lo = kKvStep, hi = (longest + kKvStep - 1) / kKvStep * kKvStep;
+    while (lo < hi) {  // smallest length with pieces_at(length) <= slots
+      const int64_t mid = (lo / kKvStep + hi / kKvStep) / 2 * kKvStep;
+      if (pieces_at(mid) <= slots_total) hi = mid; else lo = mid + kKvStep;
     }
+    split_keys = std::max<int64_t>(kMinSplitKeys, lo);
   }
+  // A chunk is a run of key steps of one unit that is handed to workgroups
+  // whole or, if cuttable, piece by piece.
   struct Piece {
-    int32_t unit, lo, hi, slot;
+    int32_t unit, lo, hi, wg;
   };
-  std::vector<Piece> pieces;
-  int64_t slots = 0;
+  const double ov = P.tile_rows == kTileRowsDecode ? kItemStepsDecode : kItemSteps;
+  auto pcost = [&](const Piece& p) { return (double)steps(p.hi - p.lo) + ov; };
+  std::vector<Piece> chunks;
+  chunks.reserve(units.size());
+  const int64_t ngroups = (int64_t)B * Hkv;
+  auto group_of = [&](const Piece& p) {
+    const Unit& u = units[(size_t)p.unit];
+    return (size_t)((int64_t)u.seq * Hkv + u.kv_head);
+  };
+  std::vector<int32_t> gptr((size_t)ngroups + 1, 0);  // chunks of a group, counted here and placed below
+  std::vector<double> gcost((size_t)ngroups, 0.0), gmax((size_t)ngroups, 0.0);
+  double total_cost = 0;
   for (size_t ui = 0; ui < units.size(); ++ui) {
     const Unit& u = units[ui];
-    int64_t nsplit = 1;
-    if (split_keys > 0) {
-      if (u.kv_hi > split_keys)
-        nsplit = (u.kv_hi + split_keys - 1) / split_keys;
+    int64_t chunk = u.kv_hi;
+    if (split_keys > 0 && u.kv_hi > split_keys) {  // equal 64-aligned chunks, the last one takes the remainder
+      const int64_t nsplit = (u.kv_hi + split_keys - 1) / split_keys;
+      chunk = steps((u.kv_hi + nsplit - 1) / nsplit) * kKvStep;
     }
-    if (nsplit <= 1) {
-      pieces.push_back(Piece{(int32_t)ui, 0, u.kv_hi, -1});
-      continue;
+    for (int64_t a = 0; a < u.kv_hi; a += chunk) {
+      const Piece p{(int32_t)ui, (int32_t)a, (int32_t)std::min<int64_t>(u.kv_hi, a + chunk), -1};
+      const size_t gi = group_of(p);
+      const double c = pcost(p);
+      chunks.push_back(p);
+      ++gptr[gi + 1];
+      gcost[gi] += c;
+      gmax[gi] = std::max(gmax[gi], c);
+      total_cost += c;
     }
-    // equal 64-aligned chunks, last one takes the remainder
-    int64_t chunk = ((u.kv_hi + nsplit - 1) / nsplit + kKvStep - 1) / kKvStep * kKvStep;
-    nsplit = (u.kv_hi + chunk - 1) / chunk;
-    const int32_t slot0 = (int32_t)slots;
-    for (int64_t k = 0; k < nsplit; ++k) {
-      const int64_t a = k * chunk, e = std::min<int64_t>(u.kv_hi, (k + 1) * chunk);
-      pieces.push_back(Piece{(int32_t)ui, (int32_t)a, (int32_t)e, (int32_t)(slots++)});
-    }
-    P.merge.push_back(MergeItem{u.seq, u.kv_head, u.row0, u.nrows, (int32_t)nsplit, slot0, 0, 0});
-    P.max_splits = std::max<int64_t>(P.max_splits, nsplit);
-    P.max_merge_rows = std::max<int32_t>(P.max_merge_rows, u.nrows * G);
   }
-  P.num_slots = slots;
-  P.workspace_bytes = slots * slot_floats(d, P.tile_rows) * (int64_t)sizeof(float);
 
-  // 5. order: groups (seq, kv head) -> XCD queues
-  const int64_t ngroups = (int64_t)B * Hkv;
-  std::vector<double> gcost((size_t)ngroups, 0.0);
-  auto pcost = [&](const Piece& p) { return (double)(steps(p.hi - p.lo) + 1); };
-  for (const Piece& p : pieces) {
-    const Unit& u = units[(size_t)p.unit];
-    gcost[(size_t)((int64_t)u.seq * Hkv + u.kv_head)] += pcost(p);
+  // 5. XCDs: a group (sequence, KV head) keeps to one XCD, whose L2 then
+  // holds its K/V, as long as that XCD's load stays within kHomeSlack of the
+  // mean.  A group that fits nowhere (few or uneven groups) is spread over
+  // the fewest XCDs that have room for it: 18 equal groups kept whole leave
+  // XCDs with three groups beside XCDs with two (prompts of 10K tokens, 2 KV
+  // heads: 2220 us whole, 1620 us spread).
+  std::vector<int32_t> gchunk(chunks.size());  // chunk ids by group, longest first
+  std::vector<int32_t> gorder;                 // groups by decreasing cost
+  {
+    for (int64_t gi = 0; gi < ngroups; ++gi) {
+      if (gptr[(size_t)gi + 1] > 0) gorder.push_back((int32_t)gi);
+      gptr[(size_t)gi + 1] += gptr[(size_t)gi];
+    }
+    std::vector<int32_t> at(gptr.begin(), gptr.end() - 1);
+    for (size_t ci = chunks.size(); ci-- > 0;)  // backwards: a group's later tiles have more keys
+      gchunk[(size_t)at[group_of(chunks[ci])]++] = (int32_t)ci;
+    auto longer = [&](int32_t a, int32_t b) {
+      return steps(chunks[(size_t)a].hi - chunks[(size_t)a].lo) > steps(chunks[(size_t)b].hi - chunks[(size_t)b].lo);
+    };
+    for (int32_t gi : gorder) {
+      auto first = gchunk.begin() + gptr[(size_t)gi], last = gchunk.begin() + gptr[(size_t)gi + 1];
+      if (!std::is_sorted(first, last, longer)) std::stable_sort(first, last, longer);
+    }
   }
-  double total_cost = 0;
-  for (double c : gcost) total_cost += c;
-  std::vector<std::vector<int32_t>> queue(kXcds);
-  std::vector<double> load(kXcds, 0.0);
-  auto least_loaded = [&]() {
-    return (int)(std::min_element(load.begin(), load.end()) - load.begin());
-  };
-  std::vector<int32_t> order(pieces.size());
-  std::iota(order.begin(), order.end(), 0);
-  // A group keeps one XCD unless it alone is a large part of an XCD's work
-  // (few groups): then its pieces are spread by cost like independent work.
-  std::vector<int64_t> gorder((size_t)ngroups);
-  std::iota(gorder.begin(), gorder.end(), 0);
   std::stable_sort(gorder.begin(), gorder.end(),
-                   [&](int64_t a, int64_t b) { return gcost[(size_t)a] > gcost[(size_t)b]; });
-  std::vector<int32_t> ghome((size_t)ngroups, -1);
-  const double big = 0.5 * total_cost / kXcds;
-  for (int64_t gi : gorder) {
-    if (gcost[(size_t)gi] <= 0 || gcost[(size_t)gi] > big) continue;
-    const int x = least_loaded();
-    ghome[(size_t)gi] = x;
-    load[(size_t)x] += gcost[(size_t)gi];
-  }
-  // pieces in XCD-assignment order: by group cost (desc), then own cost (desc), then index
-  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-    const Unit& ua = units[(size_t)pieces[(size_t)a].unit];
-    const Unit& ub = units[(size_t)pieces[(size_t)b].unit];
-    const int64_t ga = (int64_t)ua.seq * Hkv + ua.kv_head, gb = (int64_t)ub.seq * Hkv + ub.kv_head;
-    if (ga != gb && gcost[(size_t)ga] != gcost[(size_t)gb])
-      return gcost[(size_t)ga] > gcost[(size_t)gb];
-    if (ga != gb) return ga < gb;
-    return pcost(pieces[(size_t)a]) > pcost(pieces[(size_t)b]);
-  });
-  for (int32_t pi : order) {
-    const Unit& u = units[(size_t)pieces[(size_t)pi].unit];
-    const int64_t gi = (int64_t)u.seq * Hkv + u.kv_head;
-    int x = ghome[(size_t)gi];
-    if (x < 0) {
-      x = least_loaded();
-      load[(size_t)x] += pcost(pieces[(size_t)pi]);
+                   [&](int32_t a, int32_t b) { return gcost[(size_t)a] > gcost[(size_t)b]; });
+  const double mean = total_cost / kXcds;
+  const double full = mean * (1.0 + kHomeSlack), full_small = mean * (1.0 + kHomeSlackSmall);
+  std::vector<double> load(kXcds, 0.0);
+  struct Part {  // a group's chunks on one XCD: first .. last of that XCD's list
+    int32_t group;
+    size_t first, last;
+  };
+  std::vector<std::vector<int32_t>> queue(kXcds);
+  std::vector<std::vector<Part>> parts(kXcds);
+  auto place = [&](int32_t gi, bool whole) {  // whole: not at all if it does not fit one XCD
+    int by_load[kXcds];
+    std::iota(by_load, by_load + kXcds, 0);
+    std::stable_sort(by_load, by_load + kXcds, [&](int a, int b) { return load[(size_t)a] < load[(size_t)b]; });
+    if (whole && load[(size_t)by_load[0]] + gcost[(size_t)gi] > full_small) return false;
+    int k = 1;
+    if (!whole)
+      for (double room = full - load[(size_t)by_load[0]]; k < kXcds && room < gcost[(size_t)gi];)
+        room += full - load[(size_t)by_load[k++]];
+    for (int i = 0; i < k; ++i) {
+      const size_t n = queue[(size_t)by_load[i]].size();
+      parts[(size_t)by_load[i]].push_back(Part{gi, n, n});
     }
-    queue[(size_t)x].push_back(pi);
-  }
+    for (int32_t ci = gptr[(size_t)gi]; ci < gptr[(size_t)gi + 1]; ++ci) {
+      int x = by_load[0];
+      for (int i = 1; i < k; ++i)
+        if (load[(size_t)by_load[i]] < load[(size_t)x]) x = by_load[i];
+      load[(size_t)x] += pcost(chunks[(size_t)gchunk[(size_t)ci]]);
+      queue[(size_t)x].push_back(gchunk[(size_t)ci]);
+      ++parts[(size_t)x].back().last;
+    }
+    return true;
+  };
+  // small groups first, while they fit whole; the larger ones fill the rest
+  std::vector<int32_t> later;
+  for (int32_t gi : gorder)
+    if (gcost[(size_t)gi] > 0.5 * mean || !place(gi, true)) later.push_back(gi);
+  for (int32_t gi : later) place(gi, false);
+
   // 6. workgroups: one persistent workgroup per slot (256 for 256-row
-  // tiles, one per CU; 512 otherwise, two per CU), or 8 per round of the
-  // XCD queues when that is fewer.  Workgroup i runs on XCD i % 8 and works
-  // through its own list of items, so no workgroup waits for a dispatch
-  // between items.  Each XCD's pieces go, in queue order (below), to the
-  // least-loaded workgroup of that XCD (cost: key steps plus one for the
-  // per-item start-up), as a dynamic dispatch would hand them out; a
-  // workgroup runs its list in that order.  A plan with at most one piece
-  // per workgroup gets one each.
-  size_t rounds = 0;
-  for (const auto& q : queue) rounds = std::max(rounds, q.size());
-  const int64_t nwg = std::min<int64_t>(slots_total, (int64_t)rounds * kXcds);
-  std::vector<std::vector<int32_t>> wg_list((size_t)nwg);
-  std::vector<double> wg_load((size_t)nwg, 0.0);
-  // Inside each XCD the queue runs groups by decreasing longest piece (then
-  // by id), a group's pieces adjacent and longest first, so that the
-  // workgroups of an XCD work on the same groups at the same time and share
-  // their K/V in that XCD's L2; ordering by total group cost alone would
-  // leave a light group's long piece (a decode row over a long context) to
-  // run last.
-  std::vector<double> gmax((size_t)ngroups, 0.0);
-  for (const Piece& p : pieces) {
-    const Unit& u = units[(size_t)p.unit];
-    double& m = gmax[(size_t)((int64_t)u.seq * Hkv + u.kv_head)];
-    m = std::max(m, pcost(p));
-  }
+  // tiles, one per CU; 512 otherwise, two per CU), fewer for small plans.
+  // Workgroup i runs on XCD i % 8 and works through its own list of items,
+  // so no workgroup waits for a dispatch between items.  Each XCD's chunks
+  // go to the least-loaded workgroup of that XCD, groups by decreasing
+  // longest chunk (then by id) and a group's chunks longest first, so that
+  // the workgroups of an XCD work on the same groups at the same time and
+  // share their K/V in that XCD's L2, and no long piece is left for the end.
+  // A chunk that would fill a workgroup past the XCD's mean load is cut
+  // there and its remainder goes back to the group's queue: a few cut units
+  // even out the workgroups, where cutting every long unit sends more
+  // partial results through the workspace (20 mixed sequences up to 4.6K,
+  // 64 heads: 150 us with 512 of 944 units cut, 118 us with 240).
+  const int wgs_per_xcd = (int)(slots_total / kXcds);
+  // a cut adds at most two partials: all of them fit the workspace of msa_forward_noalloc
+  int64_t cuts_left = (int64_t)(MSA_NOALLOC_WORKSPACE_BYTES / sizeof(float)) / slot_floats(d, P.tile_rows) / 2;
+  std::vector<Piece> pieces;
+  pieces.reserve(chunks.size() + (size_t)slots_total);
+  std::vector<int32_t> unit_count(units.size(), 0);
   for (int x = 0; x < kXcds; ++x) {
-    auto& qx = queue[(size_t)x];
-    std::stable_sort(qx.begin(), qx.end(), [&](int32_t a, int32_t b) {
-      const Piece& pa = pieces[(size_t)a];
-      const Piece& pb = pieces[(size_t)b];
-      const Unit& ua = units[(size_t)pa.unit];
-      const Unit& ub = units[(size_t)pb.unit];
-      const int64_t ga = (int64_t)ua.seq * Hkv + ua.kv_head, gb = (int64_t)ub.seq * Hkv + ub.kv_head;
-      if (gmax[(size_t)ga] != gmax[(size_t)gb]) return gmax[(size_t)ga] > gmax[(size_t)gb];
-      if (ga != gb) return ga < gb;
-      return pcost(pa) > pcost(pb);
+    const auto& qx = queue[(size_t)x];
+    auto& px = parts[(size_t)x];
+    std::stable_sort(px.begin(), px.end(), [&](const Part& a, const Part& b) {
+      const double ma = gmax[(size_t)a.group], mb = gmax[(size_t)b.group];
+      return ma != mb ? ma > mb : a.group < b.group;
     });
-    for (int32_t pi : qx) {
-      int64_t best = -1;
-      for (int64_t wgi = x; wgi < nwg; wgi += kXcds)
-        if (best < 0 || wg_load[(size_t)wgi] < wg_load[(size_t)best]) best = wgi;
-      wg_list[(size_t)best].push_back(pi);
-      wg_load[(size_t)best] += pcost(pieces[(size_t)pi]);
+    // capacity of a workgroup before a chunk is cut
+    double capacity = 0.0;
+    if (cut_to_fit) {
+      auto pieces_at = [&](int64_t len) {
+        int64_t c = 0;
+        for (int32_t ci : qx) c += (steps(chunks[(size_t)ci].hi) + len - 1) / len;
+        return c;
+      };
+      int64_t key_steps = 0, longest = kMinSplitSteps;
+      for (int32_t ci : qx) {
+        key_steps += steps(chunks[(size_t)ci].hi);
+        longest = std::max(longest, steps(chunks[(size_t)ci].hi));
+      }
+      // the mean load, counting the items that cuts at that load would add
+      double mean_load = load[(size_t)x] / wgs_per_xcd;
+      if ((double)longest + ov > mean_load)
+        for (int it = 0; it < 2; ++it) {
+          const int64_t len = std::max<int64_t>(kMinSplitSteps, (int64_t)(mean_load - ov));
+          const double items = std::min((double)pieces_at(len), (double)qx.size() + wgs_per_xcd);
+          mean_load = ((double)key_steps + ov * items) / wgs_per_xcd;
+        }
+      // where no chunk has to be cut, a cut must also win back the merge launch
+      capacity = mean_load * (1.0 + kCutSlack) + ((double)longest + ov > mean_load ? 1.0 : kItemSteps);
+      // few chunks: the shortest length whose pieces take one workgroup
+      // each, if that is no longer than packing them would take
+      if ((int64_t)qx.size() <= wgs_per_xcd) {
+        int64_t lo = kMinSplitSteps, hi = longest;
+        while (lo < hi) {
+          const int64_t mid = (lo + hi) / 2;
+          if (pieces_at(mid) <= wgs_per_xcd) hi = mid; else lo = mid + 1;
+        }
+        if ((double)lo + ov <= kOneRoundFactor * capacity) capacity = (double)lo + ov;
+      }
+      capacity = std::max(capacity, kMinSplitSteps + ov);
+    }
+    typedef std::pair<double, int> Slot;  // (load, workgroup of this XCD): least loaded first, then lowest
+    std::priority_queue<Slot, std::vector<Slot>, std::greater<Slot>> slots;
+    for (int i = 0; i < wgs_per_xcd; ++i) slots.push(Slot(0.0, i));
+    auto shorter = [&](const Piece& a, const Piece& b) { return a.hi - a.lo < b.hi - b.lo; };
+    std::priority_queue<Piece, std::vector<Piece>, decltype(shorter)> tails(shorter);
+    for (const Part& part : px) {
+      for (size_t qi = part.first; qi < part.last || !tails.empty();) {
+        // the longest of the group's remaining chunks and cut-off tails
+        Piece p;
+        if (qi < part.last && (tails.empty() || !shorter(chunks[(size_t)qx[qi]], tails.top()))) {
+          p = chunks[(size_t)qx[qi++]];
+        } else {
+          p = tails.top();
+          tails.pop();
+        }
+        Slot s0 = slots.top();
+        slots.pop();
+        const int64_t n = steps(p.hi - p.lo);
+        if (cut_to_fit && cuts_left > 0 && n > kMinSplitSteps && s0.first + (double)n + ov > capacity) {
+          --cuts_left;
+          const int64_t fit = (int64_t)(capacity - s0.first - ov);
+          const int64_t take = std::min(std::max(fit, kMinTailSteps), n - kMinTailSteps);
+          const int32_t mid = (int32_t)(p.lo + take * kKvStep);
+          tails.push(Piece{p.unit, mid, p.hi, -1});
+          p.hi = mid;
+        }
+        p.wg = s0.second * kXcds + x;
+        pieces.push_back(p);
+        ++unit_count[(size_t)p.unit];
+        s0.first += pcost(p);
+        slots.push(s0);
+      }
     }
   }
-  // trailing workgroups with nothing to do are not launched
-  int64_t launched = nwg;
-  while (launched > 0 && wg_list[(size_t)launched - 1].empty()) --launched;
-  P.wg_ptr.assign(1, 0);
-  P.work.reserve(pieces.size());
-  for (int64_t wgi = 0; wgi < launched; ++wgi) {
-    for (int32_t pi : wg_list[(size_t)wgi]) {
-      const Piece& p = pieces[(size_t)pi];
+  // workspace slots of the split units, in unit and key order
+  std::vector<int32_t> unit_slot0(units.size(), -1);
+  for (size_t ui = 0; ui < units.size(); ++ui) {
+    const int32_t n = unit_count[ui];
+    if (n < 2) continue;
+    const Unit& u = units[ui];
+    unit_slot0[ui] = (int32_t)P.num_slots;
+    P.merge.push_back(MergeItem{u.seq, u.kv_head, u.row0, u.nrows, n, (int32_t)P.num_slots, 0, 0});
+    P.max_splits = std::max<int64_t>(P.max_splits, n);
+    P.max_merge_rows = std::max<int32_t>(P.max_merge_rows, u.nrows * G);
+    P.num_slots += n;
+  }
+  P.workspace_bytes = P.num_slots * slot_floats(d, P.tile_rows) * (int64_t)sizeof(float);
+  std::vector<int32_t> slot_lo((size_t)P.num_slots);  // first key of each slot's piece
+  {
+    std::vector<int32_t> filled(units.size(), 0);
+    for (const Piece& p : pieces)
+      if (unit_slot0[(size_t)p.unit] >= 0)
+        slot_lo[(size_t)(unit_slot0[(size_t)p.unit] + filled[(size_t)p.unit]++)] = p.lo;
+    for (const MergeItem& m : P.merge)
+      std::sort(slot_lo.begin() + m.slot0, slot_lo.begin() + m.slot0 + m.nsplit);
+  }
+  // the items by workgroup, in run order; trailing workgroups with nothing to do are not launched
+  int32_t launched = 0;
+  for (const Piece& p : pieces) launched = std::max(launched, p.wg + 1);
+  P.wg_ptr.assign((size_t)launched + 1, 0);
+  for (const Piece& p : pieces) ++P.wg_ptr[(size_t)p.wg + 1];
+  for (int32_t i = 0; i < launched; ++i) P.wg_ptr[(size_t)i + 1] += P.wg_ptr[(size_t)i];
+  P.work.resize(pieces.size());
+  {
+    std::vector<int32_t> at(P.wg_ptr.begin(), P.wg_ptr.end() - 1);
+    for (const Piece& p : pieces) {
       const Unit& u = units[(size_t)p.unit];
-      P.work.push_back(WorkItem{u.seq, u.kv_head, u.row0, u.nrows, p.lo, p.hi, p.slot, (int32_t)wgi});
+      int32_t slot = unit_slot0[(size_t)p.unit];
+      if (slot >= 0) {
+        const auto first = slot_lo.begin() + slot;
+        slot += (int32_t)(std::lower_bound(first, first + unit_count[(size_t)p.unit], p.lo) - first);
+      }
+      P.work[(size_t)at[(size_t)p.wg]++] =
+          WorkItem{u.seq, u.kv_head, u.row0, u.nrows, p.lo, p.hi, slot, p.wg};
     }
-    P.wg_ptr.push_back((int32_t)P.work.size());
   }
 
   // figures

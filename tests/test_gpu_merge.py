@@ -27,3 +27,19 @@ def test_merge_split_counts(oracle_lib, pieces, hq, hkv, d, tile):
     o, lse, plan = run(DeviceInstance(inst), kv_split_tokens=64, flags=tile)
     assert plan.info()["max_splits"] == pieces
     check_o(o.float().cpu().numpy(), ro, lse.cpu().numpy(), rl)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (4, 4, 64)])
+def test_units_cut_to_even_out_workgroups(oracle_lib, hq, hkv, d):
+    """An automatic plan whose long units are cut at uneven places, some more
+    than once, beside whole units; every row of one head per KV head."""
+    L = 6011
+    inst = workloads.make_layout(77, [L, 900], [[(100, 300), (L - 500, 500)], [(0, 900)]], hq, hkv, d)
+    heads_of = np.arange(0, hq, hq // hkv, dtype=np.int32)
+    rows = np.repeat(np.arange(inst.total_q, dtype=np.int64), heads_of.size)
+    heads = np.tile(heads_of, inst.total_q)
+    ro, rl = oracle_lib.forward(inst, rows=rows, heads=heads)
+    o, lse, plan = run(DeviceInstance(inst))
+    info = plan.info()
+    assert 0 < info["num_merge"] < info["num_tiles"] and info["max_splits"] > 2
+    check_o(o.float().cpu().numpy()[rows, heads], ro, lse.cpu().numpy()[rows, heads], rl)

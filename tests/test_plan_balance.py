@@ -1,0 +1,67 @@
+"""CPU tests of the planner's load balance: units cut only where the
+workgroups' loads need it, uneven groups spread over XCDs."""
+import numpy as np
+import pytest
+
+import paper_2606_02964_amd as msa
+from test_abi_host import _descriptors, check_plan, host_plan
+
+#: the cost of an item beside its key steps, as the planner counts it
+ITEM_STEPS = 4.0
+
+
+def _loads(plan, slots):
+    info = plan.info()
+    row_pos, work, merge = msa.msa_plan_export(plan)
+    cost = (work[:, 5] - work[:, 4] + 63) // 64 + ITEM_STEPS
+    return info, row_pos, work, merge, np.bincount(work[:, 7], weights=cost, minlength=slots)
+
+
+CASES = [
+    # contexts, segments, Hq, Hkv, d, most a workgroup may hold over the mean
+    ([10240], [[(0, 5056), (10112, 128)]], 32, 8, 128, 1.12),          # long causal units, a group per XCD
+    ([10129 - 37 * b for b in range(9)], None, 8, 2, 128, 1.06),       # 18 even groups on 8 XCDs
+    ([28861], [[(7215, 304), (28253, 608)]], 8, 2, 128, 1.20),         # few units, each far longer than the mean
+    ([10336, 10299, 10262], None, 16, 16, 64, 1.06),                   # 48 groups
+    ([4643, 900, 2100, 333, 1800, 4000], [[(4000, 643)], [(899, 1)], [(2000, 100)], [(332, 1)], [(1, 1799)],
+                                          [(3999, 1)]], 64, 8, 128, 1.35),
+]
+
+
+def _inst(lens, segs, hq, hkv, d):
+    inst = _descriptors(lens, segs, hq, hkv, d)
+    inst.total_q = int(inst.seg_len.sum())
+    inst.segments = lambda b: segs[b]
+    return inst
+
+
+@pytest.mark.parametrize("lens,segs,hq,hkv,d,most", CASES)
+def test_workgroup_loads_are_even(lens, segs, hq, hkv, d, most):
+    inst = _inst(lens, segs or [[(0, n)] for n in lens], hq, hkv, d)
+    plan = host_plan(msa, inst)
+    slots = 256 if plan.info()["tile_rows"] == 256 else 512
+    info, row_pos, work, merge, load = _loads(plan, slots)
+    check_plan(inst, row_pos, work, merge, info, hq // hkv)
+    assert load.max() <= most * load.sum() / slots
+
+
+@pytest.mark.parametrize("tile", [msa.MSA_PLAN_TILE_ROWS_128, msa.MSA_PLAN_TILE_ROWS_256])
+@pytest.mark.parametrize("tokens", [2000, 4096, 8000, 8200, 12000])
+def test_partials_of_cut_units_fit_the_noalloc_workspace(tokens, tile):
+    """One sequence of 131072 keys whose units number about one to two per
+    workgroup: every partial of the cuts fits the 64 MiB workspace of the
+    call that allocates nothing."""
+    L = 131072
+    inst = _inst([L], [[(L - tokens, tokens)]], 8, 2, 128)
+    info = host_plan(msa, inst, flags=tile).info()
+    assert info["workspace_bytes"] <= msa.MSA_NOALLOC_WORKSPACE_BYTES
+
+
+def test_short_units_are_not_cut():
+    """Units of up to 1024 keys stay whole however few there are, and
+    MSA_PLAN_NO_AUTO_SPLIT keeps every unit whole."""
+    inst = _descriptors([1024], [[(448, 576)]], 32, 8, 128)
+    assert host_plan(msa, inst).info()["num_merge"] == 0
+    long = _descriptors([30000], [[(29000, 1000)]], 32, 8, 128)
+    assert host_plan(msa, long).info()["num_merge"] > 0
+    assert host_plan(msa, long, flags=msa.MSA_PLAN_NO_AUTO_SPLIT).info()["num_merge"] == 0
