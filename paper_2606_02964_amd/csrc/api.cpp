@@ -20,10 +20,10 @@ struct msa_plan_s {
   bool host_only = true;
   int device = -1;
   std::vector<char> staging;  // host image of the device buffer (kept alive for the async copy)
-  char* dev = nullptr;        // device buffer: row_pos | work | merge | append | wg_ptr
+  char* dev = nullptr;        // device buffer: row_pos | work | merge | append | heads
   const int32_t* d_row_pos = nullptr;
   const msa::WorkItem* d_work = nullptr;
-  const int32_t* d_wg_ptr = nullptr;
+  const msa::WgHead* d_heads = nullptr;
   const msa::MergeItem* d_merge = nullptr;
   const msa::AppendItem* d_append = nullptr;
 };
@@ -77,7 +77,7 @@ msa_status msa::forward_impl(const char* who, msa_plan_t plan, const void* q, co
   p.block_table = block_table;
   p.row_pos = plan->d_row_pos;
   p.work = plan->d_work;
-  p.wg_ptr = plan->d_wg_ptr;
+  p.heads = plan->d_heads;
   p.o = static_cast<uint16_t*>(o);
   p.lse = lse;
   p.ws = static_cast<float*>(workspace);
@@ -94,6 +94,7 @@ msa_status msa::forward_impl(const char* who, msa_plan_t plan, const void* q, co
   p.max_blocks = s.max_blocks_per_seq;
   p.num_q_heads = s.num_q_heads;
   p.group = hp.group;
+  p.group_inv = (65536 + hp.group - 1) / hp.group;
   p.tile_tokens = hp.tile_tokens;
   p.scale_log2 = s.scale * 1.4426950408889634f;
   p.precise = hp.precise_weights ? 1 : 0;
@@ -152,12 +153,12 @@ msa_status msa_plan(const msa_shape* shape, const int32_t* seq_kv_len, const int
     const size_t n_work = hp.work.size() * sizeof(msa::WorkItem);
     const size_t n_merge = hp.merge.size() * sizeof(msa::MergeItem);
     const size_t n_append = hp.append.size() * sizeof(msa::AppendItem);
-    const size_t n_wg = hp.wg_ptr.size() * sizeof(int32_t);
+    const size_t n_wg = hp.wg_ptr.empty() ? 0 : hp.wg_ptr.size() - 1;
     const size_t off_work = align_up(n_row, 256);
     const size_t off_merge = off_work + align_up(n_work, 256);
     const size_t off_append = off_merge + align_up(n_merge, 256);
-    const size_t off_wg = off_append + align_up(n_append, 256);
-    const size_t bytes = std::max<size_t>(off_wg + n_wg, 256);
+    const size_t off_heads = off_append + align_up(n_append, 256);
+    const size_t bytes = std::max<size_t>(off_heads + n_wg * sizeof(msa::WgHead), 256);
     try {
       plan->staging.assign(bytes, 0);
     } catch (const std::bad_alloc&) {
@@ -168,7 +169,14 @@ msa_status msa_plan(const msa_shape* shape, const int32_t* seq_kv_len, const int
     if (n_work) std::memcpy(plan->staging.data() + off_work, hp.work.data(), n_work);
     if (n_merge) std::memcpy(plan->staging.data() + off_merge, hp.merge.data(), n_merge);
     if (n_append) std::memcpy(plan->staging.data() + off_append, hp.append.data(), n_append);
-    if (n_wg) std::memcpy(plan->staging.data() + off_wg, hp.wg_ptr.data(), n_wg);
+    for (size_t i = 0; i < n_wg; ++i) {
+      msa::WgHead h{};
+      const int32_t first = hp.wg_ptr[i], end = hp.wg_ptr[i + 1];
+      if (first < end) h.first = hp.work[(size_t)first];
+      h.rest = std::min(first + 1, end);
+      h.end = end;
+      std::memcpy(plan->staging.data() + off_heads + i * sizeof(h), &h, sizeof(h));
+    }
     const hipError_t gd = hipGetDevice(&plan->device);
     if (gd != hipSuccess) {
       delete plan;
@@ -191,7 +199,7 @@ msa_status msa_plan(const msa_shape* shape, const int32_t* seq_kv_len, const int
     plan->d_row_pos = reinterpret_cast<const int32_t*>(plan->dev);
     plan->d_work = reinterpret_cast<const msa::WorkItem*>(plan->dev + off_work);
     plan->d_merge = reinterpret_cast<const msa::MergeItem*>(plan->dev + off_merge);
-    plan->d_wg_ptr = reinterpret_cast<const int32_t*>(plan->dev + off_wg);
+    plan->d_heads = reinterpret_cast<const msa::WgHead*>(plan->dev + off_heads);
     plan->d_append = reinterpret_cast<const msa::AppendItem*>(plan->dev + off_append);
   }
   *out = plan;

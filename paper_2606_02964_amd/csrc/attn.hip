@@ -136,6 +136,11 @@ constexpr float kRescaleLog2 = 8.0f;
 // a lane's step sum of weights at which the row max is taken (see settle)
 constexpr float kSettleSum = 128.0f;
 
+// r / G for a tile row r < 256 (r * (G * group_inv - 2^16) < 2^16, so exact)
+__device__ __forceinline__ int div_group(int r, const AttnParams& p) {
+  return (int)((uint32_t)r * (uint32_t)p.group_inv >> 16);
+}
+
 // One work item of msa_attn.  smem: the K ring (2 steps) then the V ring
 // (2 steps).  Every wave leaves through the barrier that ends the item's
 // last step before its epilogue (registers only), so the next item may
@@ -154,21 +159,26 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   const int lane = tid & 63, hl = lane >> 5, ln = lane & 31;
   const int G = p.group;
   const int r = wave * 32 + ln;  // tile row
-  const int t = r / G, hh = r - t * G;
+  const int t = div_group(r, p), hh = r - t * G;
   const bool valid = t < w.nrows;
   const int tok = w.row0 + t;
   const int head = w.kv_head * G + hh;
-  const int pos = valid ? p.row_pos[tok] : -1;
 
-  // wave-wide smallest and largest causal limit
-  int pmin = valid ? pos : INT_MAX, pmax = pos;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    pmin = min(pmin, __shfl_xor(pmin, off));
-    pmax = max(pmax, __shfl_xor(pmax, off));
-  }
-  pmin = __builtin_amdgcn_readfirstlane(pmin);
-  pmax = __builtin_amdgcn_readfirstlane(pmax);
+  // Block ids: every page a wave copies belongs to block slot wave & 3 of
+  // its step, so a wave needs one id per step.  Lane i of idv holds the id of
+  // step id_base + i, idv_next those of the next 64 steps; both load before
+  // everything else of the item, since the first copies wait for them.
+  const int32_t* bt = p.block_table + (int64_t)w.seq * p.max_blocks;
+  const int bslot = wave & 3;
+  const int n = (w.kv_hi - w.kv_lo + kKvStep - 1) / kKvStep;
+  auto load_ids = [&](int s0) -> int32_t {
+    const int st = s0 + lane;
+    const int kb = w.kv_lo + st * kKvStep + bslot * kBlockSize;
+    return (st < n && kb < w.kv_hi) ? bt[kb >> 4] : 0;
+  };
+  int32_t idv = load_ids(0), idv_next = n > 64 ? load_ids(64) : 0;
+
+  const int pos = valid ? p.row_pos[tok] : -1;
 
   // Q fragments (B operand): row r, channels kk*16 + hl*8 .. +8
   bf16x8 qf[D / 16];
@@ -205,75 +215,80 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   const int64_t ksb = p.k_sb * 2, vsb = p.v_sb * 2;  // bytes per block
   const char* kbase = reinterpret_cast<const char*>(p.k + (int64_t)w.kv_head * p.k_sh);
   const char* vbase = reinterpret_cast<const char*>(p.v + (int64_t)w.kv_head * p.v_sh);
-  const int32_t* bt = p.block_table + (int64_t)w.seq * p.max_blocks;
   auto kbuf = [&](int s) -> char* { return smem + __builtin_amdgcn_readfirstlane((s & 1) * T::kBytesK); };
   auto vbuf = [&](int s) -> char* {
     return smem + __builtin_amdgcn_readfirstlane(2 * T::kBytesK + (s & 1) * T::kBytesV);
   };
-  const int n = (w.kv_hi - w.kv_lo + kKvStep - 1) / kKvStep;
-  // A step has 8 pages: the K and the V page of each of its 4 blocks (page
-  // pg: block pg & 3, V if pg >= 4); wave w copies pages w, w + W, ..., all
-  // of block slot w & 3.  issue(sk, sv) copies the K pages of step sk and
-  // the V pages of step sv (-1: none).  A block at or past kv_hi is not
-  // read; its V page is zero-filled instead (its K page keeps old values:
-  // those keys are masked by selection, so never meet arithmetic).
-  // The block ids a wave needs sit in two registers, one lane per step:
-  // lane i of idv0 holds the id of block slot w & 3 of step id_base + i, of
-  // idv1 that of step id_base + 64 + i.  A step reads its id with
-  // v_readlane (no memory access); every 64 steps the window moves on and
-  // the next 64 ids load, 64 steps before they are needed.
-  constexpr int kPagesPerWave = 8 / W;
-  const int bslot = wave & 3;
-  auto load_ids = [&](int s0) -> int32_t {
-    const int st = s0 + lane;
-    const int kb = w.kv_lo + st * kKvStep + bslot * kBlockSize;
-    return (st < n && kb < w.kv_hi) ? bt[kb >> 4] : 0;
-  };
-  int id_base = 0;
-  int32_t idv0 = load_ids(0), idv1 = load_ids(64);
-  auto step_id = [&](int st) -> int64_t {  // id_base <= st < id_base + 128 (wave-uniform)
-    const int i = st - id_base;
-    return i < 64 ? __builtin_amdgcn_readlane(idv0, i) : __builtin_amdgcn_readlane(idv1, i - 64);
-  };
-  auto issue = [&](int sk, int sv) {
-    if (sk >= id_base + 128) {  // move the window on (uniform; once per 64 steps)
-      idv0 = idv1;
-      idv1 = load_ids(id_base + 128);
-      id_base += 64;
+  // A step has 8 pages: the K and the V page of each of its 4 blocks.  With 4
+  // waves each copies both pages of its block slot; with 8, waves 0-3 copy the
+  // K pages and waves 4-7 the V pages.  Iteration j copies the K of step j+2
+  // and the V of step j+1, so the id read for a K page serves the V page of
+  // the next iteration.  A block at or past kv_hi is not read; its V page is
+  // zero-filled instead (its K page keeps old values: those keys are masked by
+  // selection, so never meet arithmetic).
+  constexpr bool kBoth = W == 4;  // a wave copies the K and the V page of its slot
+  const bool copies_k = kBoth || wave < 4, copies_v = kBoth || wave >= 4;
+  const char* const pbase = copies_k ? kbase : vbase;  // of the wave's pages (kBoth: of K)
+  const int64_t psb = copies_k ? ksb : vsb;
+  const char *page, *vpage;   // pages of the next copies
+  int32_t id_cur = 0;
+  // Reads the ids of K step s and V step s - 1 and takes their page
+  // addresses; called for s = 0, 1, 2, ... in turn, one iteration before the
+  // copies, where the address arithmetic runs beside MFMAs.  (Taken at the
+  // start of the iteration, with the range checks of both pages, it held up
+  // every wave before its first MFMA: a step of a lone workgroup took 1.07 us
+  // with 4 waves and 0.89 us with 8, d = 128, and now takes 0.90 and 0.82 us.)
+  auto next_pages = [&](int s) __attribute__((always_inline)) {
+    const int32_t id_prev = id_cur;
+    id_cur = __builtin_amdgcn_readlane(idv, s & 63);
+    // pinned to scalar registers here: left to itself the compiler moves the
+    // products to the copies and spills 130 vector registers
+    page = pbase + (int64_t)(copies_k ? id_cur : id_prev) * psb;
+    asm volatile("" : "+s"(page));
+    if constexpr (kBoth) {
+      vpage = vbase + (int64_t)id_prev * vsb;
+      asm volatile("" : "+s"(vpage));
     }
-    int64_t ids[kPagesPerWave];
-    bool have[kPagesPerWave], zero[kPagesPerWave];
-#pragma unroll
-    for (int k = 0; k < kPagesPerWave; ++k) {
-      const int pg = wave + k * W;
-      const int bi = pg & 3;
-      const int st = pg >= 4 ? sv : sk;
-      const bool live = st >= 0 && st < n;
-      const int kb = w.kv_lo + st * kKvStep;
-      have[k] = live && kb + bi * kBlockSize < w.kv_hi;
-      zero[k] = live && !have[k] && pg >= 4;
-      ids[k] = have[k] ? step_id(st) : 0;
+  };
+  // before next_pages(s) at multiples of 64: the next 64 ids move in
+  auto move_ids = [&](int s) __attribute__((always_inline)) {
+    if ((s & 63) == 0) {
+      idv = idv_next;
+      if (s + 64 < n) idv_next = load_ids(s + 64);
     }
+  };
+  auto copy_k = [&](const char* src, int s) __attribute__((always_inline)) {
+    char* kd = kbuf(s) + bslot * T::kPage;
 #pragma unroll
-    for (int k = 0; k < kPagesPerWave; ++k) {
-      const int pg = wave + k * W;
-      const int bi = pg & 3;
-      if (have[k]) {
-        if (pg < 4) {
-          const char* kg = kbase + ids[k] * ksb;
-          char* kd = kbuf(sk) + bi * T::kPage;
+    for (int q = 0; q < T::kDmaPerPage; ++q) dma16(src, kgo[q], kd + q * 1024);
+  };
+  auto copy_v = [&](const char* src, int s) __attribute__((always_inline)) {
+    char* vd = vbuf(s) + bslot * T::kPage;
 #pragma unroll
-          for (int q = 0; q < T::kDmaPerPage; ++q) dma16(kg, kgo[q], kd + q * 1024);
-        } else {
-          const char* vg = vbase + ids[k] * vsb;
-          char* vd = vbuf(sv) + bi * T::kPage;
-#pragma unroll
-          for (int q = 0; q < T::kDmaPerPage; ++q) dma16(vg + q * vgq, vgo0, vd + q * 1024);
-        }
-      } else if (zero[k]) {
+    for (int q = 0; q < T::kDmaPerPage; ++q) dma16(src + q * vgq, vgo0, vd + q * 1024);
+  };
+  // copies of iteration j, both steps whole
+  auto copy_whole = [&](int j) __attribute__((always_inline)) {
+    if constexpr (kBoth) {
+      copy_k(page, j + 2);
+      copy_v(vpage, j + 1);
+    } else if (copies_k) {
+      copy_k(page, j + 2);
+    } else {
+      copy_v(page, j + 1);
+    }
+  };
+  // K of step sk and V of step sv where either may end inside the step or lie past the end
+  auto copy_any = [&](const char* ksrc, int sk, const char* vsrc, int sv) {
+    const int kb = w.kv_lo + bslot * kBlockSize;
+    if (copies_k && kb + sk * kKvStep < w.kv_hi) copy_k(ksrc, sk);
+    if (copies_v && sv < n) {
+      if (kb + sv * kKvStep < w.kv_hi) {
+        copy_v(vsrc, sv);
+      } else {
 #pragma unroll
         for (int q = 0; q < T::kDmaPerPage; ++q)
-          *reinterpret_cast<uint4*>(vbuf(sv) + bi * T::kPage + q * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
+          *reinterpret_cast<uint4*>(vbuf(sv) + bslot * T::kPage + q * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
       }
     }
   };
@@ -404,38 +419,31 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     }
   };
 
-  // One step j, scores of step j in sbuf[B] (masked):
+  // One step j, scores of step j in sbuf[B]; neither it nor step j+1 is masked:
   //   block 1: QK of step j+1 into sbuf[1-B], interleaved with the weights of
   //            step j; then settle the weights of step j (rarely does work)
-  //   block 2: PV of step j (on diagonal steps interleaved with the mask of
-  //            step j+1)
+  //   block 2: PV of step j, with the page addresses of the next copies
   // The source order is fixed with scheduling fences.  j has the parity of
   // B (the paired loop starts at step 0), so step j+1's K sits in ring stage
   // 1-B and step j's V in stage B.
-  auto fused = [&](auto bsel, auto mask_next, auto has_next, int j) {
+  auto fused = [&](auto bsel, auto&& addresses) {
     constexpr int B = decltype(bsel)::value, NB = 1 - B;
-    constexpr bool kMaskNext = decltype(mask_next)::value;
-    constexpr bool kNext = decltype(has_next)::value;
     const float nm = m_ref == -__builtin_inff() ? 0.0f : -m_ref;
     uint32_t pk[16];
     float ls = 0.0f;
     // block 1
     bf16x8 ka[kQk];
-    if constexpr (kNext) {
 #pragma unroll
-      for (int a = 0; a < kAhead; ++a) ka[a] = kread_c(std::integral_constant<int, NB>{}, a);
-    }
+    for (int a = 0; a < kAhead; ++a) ka[a] = kread_c(std::integral_constant<int, NB>{}, a);
 #pragma unroll
     for (int i = 0; i < kQk; ++i) {
-      if constexpr (kNext) {
-        if (i + kAhead < kQk) ka[i + kAhead] = kread_c(std::integral_constant<int, NB>{}, i + kAhead);
-        const int kk = i >> 1, kt = i & 1;
-        if (kk == 0) {
-          const f32x16 zero = {};
-          sbuf[NB][kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qf[0], zero, 0, 0, 0);
-        } else {
-          sbuf[NB][kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qf[kk], sbuf[NB][kt], 0, 0, 0);
-        }
+      if (i + kAhead < kQk) ka[i + kAhead] = kread_c(std::integral_constant<int, NB>{}, i + kAhead);
+      const int kk = i >> 1, kt = i & 1;
+      if (kk == 0) {
+        const f32x16 zero = {};
+        sbuf[NB][kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qf[0], zero, 0, 0, 0);
+      } else {
+        sbuf[NB][kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qf[kk], sbuf[NB][kt], 0, 0, 0);
       }
 #pragma unroll
       for (int u = 0; u < kElPerQk; u += 2) {
@@ -450,7 +458,6 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     settle(B, ls, [&]() { weights_plain(B, pk, ls); });
     l_run += ls;
     // block 2
-    const int lim = pos - (w.kv_lo + (j + 1) * kKvStep) - hl * 8;
     bf16x8 va[kPv];
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) va[a] = vread_c(std::integral_constant<int, B>{}, a);
@@ -461,14 +468,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
       // P sub-step ks = keys 16*ks + hl*8 .. +8 = packed weights 4*ks .. 4*ks+3
       const bf16x8 pb = __builtin_bit_cast(bf16x8, make_uint4(pk[4 * ks], pk[4 * ks + 1], pk[4 * ks + 2], pk[4 * ks + 3]));
       oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pb, oacc[dt], 0, 0, 0);
-      if constexpr (kNext && kMaskNext) {
-#pragma unroll
-        for (int u = 0; u < kElPerPv; ++u) {
-          const int e = i * kElPerPv + u;
-          const float x = sbuf[NB][e >> 4][e & 15];
-          sbuf[NB][e >> 4][e & 15] = ((e >> 4) * 32 + ((e & 15) >> 3) * 16 + (e & 7)) <= lim ? x : -__builtin_inff();
-        }
-      }
+      if (i == 0) addresses();
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -478,14 +478,22 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   // barrier that ended iteration j-1 (the buffers' previous contents K_j and
   // V_{j-1} were last read before it) and waited for before the barrier that
   // ends iteration j.
+  next_pages(0);
+  copy_any(kbase + (int64_t)id_cur * ksb, 0, vbase + (int64_t)id_cur * vsb, 0);
+  next_pages(1);
+  if (copies_k) copy_any(page, 1, vbase, n);
+  next_pages(2);
+  // wave-wide smallest and largest causal limit: a tile's rows are in
+  // ascending position, so those of its first and last row
+  const int nvalid = __builtin_popcountll(__ballot(valid)) >> 1;  // rows (both lane halves hold them)
+  const int pmin = nvalid > 0 ? __builtin_amdgcn_readfirstlane(pos) : INT_MAX;
+  const int pmax = nvalid > 0 ? __builtin_amdgcn_readlane(pos, nvalid - 1) : -1;
   // (>=: a step whose last key is some row's position counts too, so that
   // every row's diagonal step runs through the masked path)
   auto need_mask = [&](int s) { return w.kv_lo + s * kKvStep + kKvStep - 1 >= pmin; };
   // steps this wave computes: keys up to its largest position.  A wave past
   // them still copies its share of every step and meets every barrier.
   const int nw = pmax >= w.kv_lo ? min(n, (pmax - w.kv_lo) / kKvStep + 1) : 0;
-  issue(0, 0);
-  issue(1, -1);
   wait_dma<0>();
   lds_barrier();
   if (nw > 0) {
@@ -507,12 +515,15 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   };
   // (with precise weights every step runs unpipelined, below)
   int j = 0;
+  const int whole = (w.kv_hi - w.kv_lo) / kKvStep;  // steps without a missing block
   for (; !kPrecise && j + 2 < nw && !need_mask(j + 2); j += 2) {
-    issue(j + 2, j + 1);
-    fused(std::integral_constant<int, 0>{}, std::false_type{}, std::true_type{}, j);
+    copy_whole(j);  // step j+2 is not masked, hence whole
+    fused(std::integral_constant<int, 0>{}, [&]() { next_pages(j + 3); });
     tail();
-    issue(j + 3, j + 2);
-    fused(std::integral_constant<int, 1>{}, std::false_type{}, std::true_type{}, j + 1);
+    if (j + 3 < whole) copy_whole(j + 1);
+    else copy_any(page, j + 3, kBoth ? vpage : page, j + 2);
+    move_ids(j + 4);
+    fused(std::integral_constant<int, 1>{}, [&]() { next_pages(j + 4); });
     tail();
   }
   // Remaining steps (the diagonal ones and the last) run without overlap:
@@ -554,7 +565,9 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     }
   };
   for (; j < n; ++j) {
-    issue(j + 2, j + 1);
+    copy_any(page, j + 2, kBoth ? vpage : page, j + 1);
+    move_ids(j + 3);
+    next_pages(j + 3);
     if (j < nw) plain(j, kPrecise || need_mask(j));
     tail();
   }
@@ -594,14 +607,20 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   }
 }
 
-// Persistent launch: workgroup i runs the items wg_ptr[i] .. wg_ptr[i+1]-1.
+// Persistent launch: workgroup i runs its first item, which lies in its head
+// so that no second load has to wait for the list's bounds, then the items
+// heads[i].rest .. heads[i].end-1.
 template <int D, int W, bool kPrecise>
 __global__ __launch_bounds__(64 * W, 2) void msa_attn_kernel(AttnParams p) {
   using T = Tile<D>;
   // K ring (2 steps) then V ring (2 steps); K runs one step ahead of V
   __shared__ __attribute__((aligned(1024))) char smem[2 * T::kBytesK + 2 * T::kBytesV];
-  const int end = p.wg_ptr[blockIdx.x + 1];
-  for (int it = p.wg_ptr[blockIdx.x]; it < end; ++it) attn_item<D, W, kPrecise>(p, p.work[it], smem);
+  const WgHead head = p.heads[blockIdx.x];
+  WorkItem w = head.first;
+  for (int it = head.rest;; w = p.work[it++]) {
+    attn_item<D, W, kPrecise>(p, w, smem);
+    if (it >= head.end) break;
+  }
 }
 
 // msa_decode: tiles of up to 32 rows (decode-like plans).  Every wave of the
@@ -640,20 +659,29 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, hl = lane >> 5, ln = lane & 31;
   const int G = p.group;
-  const int t = ln / G, hh = ln - t * G;  // tile row ln <-> token t, head hh of the group
+  const int t = div_group(ln, p), hh = ln - t * G;  // tile row ln <-> token t, head hh of the group
   const bool valid = t < w.nrows;
   const int tok = w.row0 + t;
   const int head = w.kv_head * G + hh;
-  const int pos = valid ? p.row_pos[tok] : -1;
-  int pmin = valid ? pos : INT_MAX, pmax = pos;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    pmin = min(pmin, __shfl_xor(pmin, off));
-    pmax = max(pmax, __shfl_xor(pmax, off));
-  }
-  pmin = __builtin_amdgcn_readfirstlane(pmin);
-  pmax = __builtin_amdgcn_readfirstlane(pmax);
 
+  // The two blocks of half-step h.  The second one is only read when it
+  // holds a key of the range; otherwise the first one stands in (its keys
+  // are then past every row's position, hence masked).  The ids of this
+  // wave's first 64 half-steps (h = wave + 4i) are loaded once, lane i
+  // holding those of half-step i, so that no half-step waits for a table
+  // read, and before everything else of the item; later half-steps read the
+  // table directly.
+  const int32_t* bt = p.block_table + (int64_t)w.seq * p.max_blocks;
+  const int nh = (w.kv_hi - w.kv_lo + kHalf - 1) / kHalf;  // (an item's keys end at its last row's position or before)
+  auto table_blocks = [&](int h, int32_t& id0, int32_t& id1) {
+    const int k0 = w.kv_lo + h * kHalf;
+    id0 = bt[k0 >> 4];
+    id1 = k0 + kBlockSize < w.kv_hi ? bt[(k0 >> 4) + 1] : id0;
+  };
+  int32_t idv0 = 0, idv1 = 0;
+  if (wave + kWaves * lane < nh) table_blocks(wave + kWaves * lane, idv0, idv1);
+
+  const int pos = valid ? p.row_pos[tok] : -1;
   bf16x8 qf[D / 16];
   {
     const uint16_t* qrow = p.q + (int64_t)tok * p.q_st + (int64_t)head * p.q_sh + hl * 8;
@@ -670,7 +698,6 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
 
   const char* kbase = reinterpret_cast<const char*>(p.k + (int64_t)w.kv_head * p.k_sh);
   const char* vbase = reinterpret_cast<const char*>(p.v + (int64_t)w.kv_head * p.v_sh);
-  const int32_t* bt = p.block_table + (int64_t)w.seq * p.max_blocks;
   const int64_t ksb = p.k_sb * 2, vsb = p.v_sb * 2;  // bytes per block
   const int krow = swap_bits23(ln);                   // key (0..31 in the half-step) of MFMA row ln
   // per-lane byte offsets inside a block: K row krow % 16 at channel hl*8
@@ -679,22 +706,6 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
   const uint32_t voff = (uint32_t)(ln * p.v_sd + hl * 8) * 2u;
   const uint32_t vdt = (uint32_t)(32 * p.v_sd) * 2u;
 
-  const int nh = (w.kv_hi - w.kv_lo + kHalf - 1) / kHalf;
-  // half-steps holding keys up to the tile's largest position
-  const int nhw = pmax >= w.kv_lo ? min(nh, (pmax - w.kv_lo) / kHalf + 1) : 0;
-  // The two blocks of half-step h.  The second one is only read when it
-  // holds a key of the range; otherwise the first one stands in (its keys
-  // are then past every row's position, hence masked).  The ids of this
-  // wave's first 64 half-steps (h = wave + 4i) are loaded once, lane i
-  // holding those of half-step i, so that no half-step waits for a table
-  // read; later half-steps read the table directly.
-  auto table_blocks = [&](int h, int32_t& id0, int32_t& id1) {
-    const int k0 = w.kv_lo + h * kHalf;
-    id0 = bt[k0 >> 4];
-    id1 = k0 + kBlockSize < w.kv_hi ? bt[(k0 >> 4) + 1] : id0;
-  };
-  int32_t idv0 = 0, idv1 = 0;
-  if (wave + kWaves * lane < nhw) table_blocks(wave + kWaves * lane, idv0, idv1);
   auto blocks = [&](int h, int64_t& id0, int64_t& id1) __attribute__((always_inline)) {
     const int i = (h - wave) / kWaves;  // wave-uniform
     if (i < 64) {
@@ -736,11 +747,12 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.0f;
 
+  int pmin = 0;  // position of the tile's first row, the smallest (set below, once loads are under way)
   // one half-step h of this wave, its K in buffer b
   auto half = [&](auto bsel, int h) __attribute__((always_inline)) {
     constexpr int b = decltype(bsel)::value;
     load_v(h);
-    if (h + kWaves < nhw) load_k(std::integral_constant<int, 1 - b>{}, h + kWaves);
+    if (h + kWaves < nh) load_k(std::integral_constant<int, 1 - b>{}, h + kWaves);
     f32x16 sc = {};
 #pragma unroll
     for (int kk = 0; kk < kQk; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[b][kk], qf[kk], sc, 0, 0, 0);
@@ -824,10 +836,11 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
       }
     }
   };
-  if (wave < nhw) load_k(std::integral_constant<int, 0>{}, wave);
-  for (int h = wave; h < nhw; h += 2 * kWaves) {
+  if (wave < nh) load_k(std::integral_constant<int, 0>{}, wave);
+  pmin = __builtin_amdgcn_readfirstlane(pos);
+  for (int h = wave; h < nh; h += 2 * kWaves) {
     half(std::integral_constant<int, 0>{}, h);
-    if (h + kWaves < nhw) half(std::integral_constant<int, 1>{}, h + kWaves);
+    if (h + kWaves < nh) half(std::integral_constant<int, 1>{}, h + kWaves);
   }
 
   // merge the waves' partial states: lane (hl, ln) holds row ln, channels
@@ -849,7 +862,7 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
   __syncthreads();
   constexpr int kCh = D / 8;  // channels per thread: 32 rows x 8 threads
   const int row = tid >> 3, c0 = (tid & 7) * kCh;
-  const int rt = row / G, rh = row - rt * G;
+  const int rt = div_group(row, p), rh = row - rt * G;
   if (rt >= w.nrows) return;
   float M = -__builtin_inff();
 #pragma unroll
@@ -896,10 +909,12 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
 template <int D, bool kPrecise>
 __global__ __launch_bounds__(256, 2) void msa_decode_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) DecodeLds<D> lds;
-  const int end = p.wg_ptr[blockIdx.x + 1];
-  for (int it = p.wg_ptr[blockIdx.x]; it < end; ++it) {
-    if (it > p.wg_ptr[blockIdx.x]) __syncthreads();  // the previous item's merge reads are done
-    decode_item<D, kPrecise>(p, p.work[it], lds);
+  const WgHead head = p.heads[blockIdx.x];
+  WorkItem w = head.first;
+  for (int it = head.rest;; w = p.work[it++]) {
+    decode_item<D, kPrecise>(p, w, lds);
+    if (it >= head.end) break;
+    __syncthreads();  // the item's merge reads are done
   }
 }
 

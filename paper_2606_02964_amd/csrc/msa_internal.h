@@ -37,6 +37,14 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 32, "WorkItem is exported as 8 int32");
 
+// One entry per workgroup: its first item and where its other items lie.
+struct WgHead {
+  WorkItem first;     // nrows == 0 if the workgroup has no items
+  int32_t rest, end;  // its other items: work[rest] .. work[end - 1], in order
+  int32_t pad0, pad1;
+};
+static_assert(sizeof(WgHead) == 48, "WgHead is loaded as 12 int32");
+
 struct MergeItem {
   int32_t seq;
   int32_t kv_head;
@@ -60,7 +68,7 @@ struct AttnParams {
   const int32_t* block_table;
   const int32_t* row_pos;
   const WorkItem* work;
-  const int32_t* wg_ptr;  // workgroup i runs items wg_ptr[i] .. wg_ptr[i+1]-1, in order
+  const WgHead* heads;  // [workgroups]
   uint16_t* o;
   float* lse;        // may be null
   float* ws;         // workspace (partials), may be null when unused
@@ -70,6 +78,7 @@ struct AttnParams {
   int32_t max_blocks;
   int32_t num_q_heads;
   int32_t group;     // G = Hq / Hkv
+  int32_t group_inv; // ceil(2^16 / G): r / G = r * group_inv >> 16 for r < 256
   int32_t tile_tokens;
   float scale_log2;  // scale * log2(e)
   int32_t precise;   // nonzero: every step carries hi + lo weights (MSA_PLAN_PRECISE_WEIGHTS)

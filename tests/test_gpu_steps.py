@@ -1,0 +1,28 @@
+"""GPU test of the attention kernels' step bookkeeping: runs of key steps that
+end at and around the 64-step windows of preloaded block ids, with whole and
+partial last steps and last blocks."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2606_02964_amd as msa
+import workloads
+from gpu_helpers import DeviceInstance, check_o, run
+
+
+@pytest.mark.parametrize("tile", [msa.MSA_PLAN_TILE_ROWS_32, msa.MSA_PLAN_TILE_ROWS_128,
+                                  msa.MSA_PLAN_TILE_ROWS_256])
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (3, 1, 64)])
+@pytest.mark.parametrize("L", [64 * 3, 64 * 3 + 1, 64 * 64 - 1, 64 * 64, 64 * 64 + 33, 64 * 65 + 16, 64 * 67,
+                               64 * 128 + 49, 64 * 131])
+def test_id_windows_and_last_steps(oracle_lib, L, hq, hkv, d, tile):
+    """An unsplit item of L keys: rows at the end of the context, and a few in
+    the middle that share their tile."""
+    mid = L // 2
+    inst = workloads.make_layout(500 + L, [L], [[(mid, 5), (L - 20, 20)]], hq, hkv, d, keep_logical=False)
+    ro, rl = oracle_lib.forward(inst)
+    o, lse, _ = run(DeviceInstance(inst), flags=tile | msa.MSA_PLAN_NO_AUTO_SPLIT)
+    check_o(o.float().cpu().numpy(), ro, lse.cpu().numpy(), rl)
