@@ -117,7 +117,9 @@ typedef struct msa_plan_opts {
  *     twice the rows) when the plan has many tiles and a long run of key
  *     steps per workgroup slot;
  *   - else 128-row tiles (two workgroups per CU: one's start-up and tail
- *     overlap the other's work).
+ *     overlap the other's work).  When such a plan has few short tiles, its
+ *     work items hold at most 32 rows each and run as 32-row tiles do (the
+ *     plan's tile_rows and workspace slots stay those of 128-row tiles).
  * The flags are exclusive.  32-row tiles need Hq / Hkv <= 32, 128-row tiles
  * Hq / Hkv <= 128 (else MSA_ERR_UNSUPPORTED). */
 #define MSA_PLAN_TILE_ROWS_128 4
@@ -148,7 +150,7 @@ typedef struct msa_plan_info_t {
   double tile_flops;        /* flops the tiles issue (waves holding rows), incl. masked waste */
   double planned_bytes;     /* Q + O + K/V bytes the executed tiles request */
   double min_bytes;         /* Q + O + K/V of visible keys once per (seq, kv head) */
-  int64_t tile_rows;        /* rows per tile of this plan: 32, 128 or 256 */
+  int64_t tile_rows;        /* rows per tile of this plan (the most a work item holds): 32, 128 or 256 */
   int64_t num_workgroups;   /* workgroups launched; each runs its own list of work items */
 } msa_plan_info_t;
 

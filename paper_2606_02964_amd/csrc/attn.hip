@@ -38,7 +38,8 @@
 // QK MFMAs of step j+1 are interleaved with the exponentials of step j, so
 // that each of them is followed by independent vector work.  The diagonal
 // steps and the last one run the same operations without overlap.
-// msa_decode: 32-row tiles of decode-like plans; the four waves of a
+// msa_decode: 32-row tiles of decode-like plans and 32-row items of plans with
+// few short tiles; the four waves of a
 // workgroup split the tile's keys, read K and V straight into registers and
 // merge their softmax states through LDS (see the kernel); masked
 // half-steps carry their weights as hi + lo terms, as above.
@@ -758,12 +759,12 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
     for (int kk = 0; kk < kQk; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[b][kk], qf[kk], sc, 0, 0, 0);
     // score e (0..15) of a lane is key (e / 8) * 16 + hl * 8 + e % 8 of the half-step
     const int k0 = w.kv_lo + h * kHalf;
-    // On a masked half-step (split) the rows whose diagonal half-step it is
-    // also enter their weights' bf16 lo terms, as in the main kernel: a
+    // On the two half-steps of a row's diagonal 64-key step (split) the row
+    // also enters its weights' bf16 lo terms, as in the main kernel: a
     // second PV pass on them follows (with precise weights: on every
     // half-step, for every row).
     const bool masked = k0 + kHalf - 1 >= pmin;  // holds some row's position, or passes one
-    const bool split = masked || kPrecise;
+    const bool split = (k0 | (kKvStep - 1)) >= pmin || kPrecise;
     if (masked) {
       const int lim = pos - k0 - hl * 8;
 #pragma unroll
@@ -804,7 +805,7 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
         weights();
       }
     }
-    const bool own = pos >= k0 && pos < k0 + kHalf;  // the row's diagonal half-step
+    const bool own = (pos | (kKvStep - 1)) == (k0 | (kKvStep - 1));  // the row's diagonal step
     if (split && !kPrecise) {  // the same weights in fp32, in place of the scores; hi(w) == pk
       const float nm = m_ref == -__builtin_inff() ? 0.0f : -m_ref;
 #pragma unroll
@@ -891,8 +892,8 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
                                                        pack_bf16x2(acc[q + 2] * inv, acc[q + 3] * inv));
     if (p.lse && c0 == 0) p.lse[(int64_t)otok * p.num_q_heads + ohead] = (M + __log2f(L)) * kLn2;
   } else {
-    constexpr int kR = 32;  // rows of a workspace slot of this tile width
-    float* slot = p.ws + (int64_t)w.out_slot * kR * (D + 1);
+    const int R = p.slot_rows;
+    float* slot = p.ws + (int64_t)w.out_slot * R * (D + 1);
     const bool empty = !(L > 0.0f);  // no visible key in this split
     const float inv = empty ? 0.0f : 1.0f / L;
 #pragma unroll
@@ -902,7 +903,7 @@ __device__ __forceinline__ void decode_item(const AttnParams& p, const WorkItem 
       for (int z = 0; z < 4; ++z) v[z] = acc[q + z] * inv;
       *reinterpret_cast<f32x4*>(slot + row * D + c0 + q) = v;
     }
-    if (c0 == 0) slot[kR * D + row] = empty ? -__builtin_inff() : (M + __log2f(L)) * kLn2;
+    if (c0 == 0) slot[(int64_t)R * D + row] = empty ? -__builtin_inff() : (M + __log2f(L)) * kLn2;
   }
 }
 
@@ -978,18 +979,18 @@ __global__ __launch_bounds__(256) void msa_merge_kernel(MergeParams p) {
 // The precise-weights forms are separate instantiations, so that the
 // default kernels carry no test of the flag.
 template <bool kPrecise>
-int launch_attn_form(const AttnParams& p, int head_dim, int tile_rows, int num_wg, hipStream_t s) {
-  if (head_dim == 128 && tile_rows == kTileRowsNarrow)
+int launch_attn_form(const AttnParams& p, int head_dim, int item_rows, int num_wg, hipStream_t s) {
+  if (head_dim == 128 && item_rows == kTileRowsNarrow)
     hipLaunchKernelGGL((msa_attn_kernel<128, 4, kPrecise>), dim3(num_wg), dim3(256), 0, s, p);
-  else if (head_dim == 128 && tile_rows == kTileRowsWide)
+  else if (head_dim == 128 && item_rows == kTileRowsWide)
     hipLaunchKernelGGL((msa_attn_kernel<128, 8, kPrecise>), dim3(num_wg), dim3(512), 0, s, p);
-  else if (head_dim == 64 && tile_rows == kTileRowsNarrow)
+  else if (head_dim == 64 && item_rows == kTileRowsNarrow)
     hipLaunchKernelGGL((msa_attn_kernel<64, 4, kPrecise>), dim3(num_wg), dim3(256), 0, s, p);
-  else if (head_dim == 64 && tile_rows == kTileRowsWide)
+  else if (head_dim == 64 && item_rows == kTileRowsWide)
     hipLaunchKernelGGL((msa_attn_kernel<64, 8, kPrecise>), dim3(num_wg), dim3(512), 0, s, p);
-  else if (head_dim == 128 && tile_rows == kTileRowsDecode)
+  else if (head_dim == 128 && item_rows == kTileRowsDecode)
     hipLaunchKernelGGL((msa_decode_kernel<128, kPrecise>), dim3(num_wg), dim3(256), 0, s, p);
-  else if (head_dim == 64 && tile_rows == kTileRowsDecode)
+  else if (head_dim == 64 && item_rows == kTileRowsDecode)
     hipLaunchKernelGGL((msa_decode_kernel<64, kPrecise>), dim3(num_wg), dim3(256), 0, s, p);
   else
     return (int)hipErrorInvalidValue;
@@ -998,11 +999,11 @@ int launch_attn_form(const AttnParams& p, int head_dim, int tile_rows, int num_w
 
 }  // namespace
 
-int launch_attn(const AttnParams& p, int head_dim, int tile_rows, int num_wg, void* stream) {
+int launch_attn(const AttnParams& p, int head_dim, int item_rows, int num_wg, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (num_wg <= 0) return 0;
-  return p.precise ? launch_attn_form<true>(p, head_dim, tile_rows, num_wg, s)
-                   : launch_attn_form<false>(p, head_dim, tile_rows, num_wg, s);
+  return p.precise ? launch_attn_form<true>(p, head_dim, item_rows, num_wg, s)
+                   : launch_attn_form<false>(p, head_dim, item_rows, num_wg, s);
 }
 
 int launch_merge(const MergeParams& p, int head_dim, int num_merge, void* stream) {

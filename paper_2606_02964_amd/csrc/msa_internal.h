@@ -79,7 +79,7 @@ struct AttnParams {
   int32_t num_q_heads;
   int32_t group;     // G = Hq / Hkv
   int32_t group_inv; // ceil(2^16 / G): r / G = r * group_inv >> 16 for r < 256
-  int32_t tile_tokens;
+  int32_t slot_rows; // rows of a workspace slot
   float scale_log2;  // scale * log2(e)
   int32_t precise;   // nonzero: every step carries hi + lo weights (MSA_PLAN_PRECISE_WEIGHTS)
 };
@@ -97,7 +97,8 @@ struct MergeParams {
 };
 
 // Launchers (attn.hip).  Return a hipError_t value as int.
-int launch_attn(const AttnParams& p, int head_dim, int tile_rows, int num_wg, void* stream);
+// item_rows: rows of the widest work item (32, 128 or 256), which selects the kernel.
+int launch_attn(const AttnParams& p, int head_dim, int item_rows, int num_wg, void* stream);
 int launch_merge(const MergeParams& p, int head_dim, int num_merge, void* stream);
 
 }  // namespace msa

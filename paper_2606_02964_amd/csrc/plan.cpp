@@ -16,7 +16,8 @@
 //      tail overlap the other's work, and decode-heavy plans keep more key
 //      streams in flight); it is 32 when no 128-row tile would hold more
 //      than 32 rows (decode-like plans: the four waves of a workgroup then
-//      split the tile's keys);
+//      split the tile's keys).  A 128-row plan of few short tiles runs as
+//      items of up to 32 rows, in the same way;
 //   3. units: tile x KV head, keys [0, max position in tile + 1);
 //   4. key splits of 32-row plans: the cut length is the shortest whose
 //      pieces all fit one round of the workgroup slots; other plans cut
@@ -55,6 +56,8 @@ constexpr double kWideMinStepsPerSlot = 384.0;
 constexpr double kWasteFrac = 0.125;     // masked keys allowed per tile, relative
 constexpr int64_t kMinSplitKeys = 1024;  // never split below this many keys
 constexpr int64_t kMinSplitSteps = kMinSplitKeys / kKvStep;
+constexpr int64_t kMinSplitKeysDecode = 256;  // the same for 32-row items with a CU each
+constexpr int64_t kWholeKeysDecode = 768;     // 32-row items of up to this many keys stay whole
 constexpr int64_t kMinTailSteps = kMinSplitSteps / 2;  // shortest remainder of a cut unit
 // cost of starting and ending an item, in key steps: 7-9 us against 1.9 us a
 // step (128- and 256-row tiles); small beside a streamed step of a 32-row tile
@@ -93,6 +96,7 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
   if (o.flags & ~(MSA_PLAN_HOST_ONLY | MSA_PLAN_NO_AUTO_SPLIT | MSA_PLAN_TILE_ROWS_128 |
                   MSA_PLAN_TILE_ROWS_256 | MSA_PLAN_TILE_ROWS_32 | MSA_PLAN_PRECISE_WEIGHTS))
     return fail(err, MSA_ERR_INVALID_ARG, "unknown opts.flags bits");
+  const bool forced_width = (o.flags & (MSA_PLAN_TILE_ROWS_128 | MSA_PLAN_TILE_ROWS_256 | MSA_PLAN_TILE_ROWS_32)) != 0;
   {
     const int forced = !!(o.flags & MSA_PLAN_TILE_ROWS_128) + !!(o.flags & MSA_PLAN_TILE_ROWS_256) +
                        !!(o.flags & MSA_PLAN_TILE_ROWS_32);
@@ -248,6 +252,50 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
     if (o.q_tile_tokens > P.tile_tokens)
       return fail(err, MSA_ERR_INVALID_ARG, "q_tile_tokens must be in [0, tile_rows / (Hq/Hkv)]");
     if (o.q_tile_tokens > 0) P.tile_tokens = o.q_tile_tokens;
+    P.item_rows = rows;
+  }
+  auto steps = [](int64_t keys) { return (keys + kKvStep - 1) / kKvStep; };
+  // shortest 64-aligned length >= lo that cuts the units of more than `whole`
+  // keys into at most `most` pieces, counting the uncut ones
+  auto shortest_cut = [&](const std::vector<Unit>& us, int64_t lo, int64_t whole, int64_t most) {
+    int64_t hi = lo;
+    for (const Unit& u : us) hi = std::max(hi, steps(u.kv_hi) * kKvStep);
+    while (lo < hi) {
+      const int64_t mid = (lo / kKvStep + hi / kKvStep) / 2 * kKvStep;
+      int64_t c = 0;
+      for (const Unit& u : us) c += u.kv_hi > whole ? (u.kv_hi + mid - 1) / mid : 1;
+      if (c <= most) hi = mid; else lo = mid + kKvStep;
+    }
+    return lo;
+  };
+  // Few short tiles: each 128-row tile runs as items of up to 32 rows whose
+  // four waves split the keys, while such items have a CU each.  A call that
+  // small lasts as long as its longest chain of key steps, and 128 keys of a
+  // 32-row item take as long as 64 of a 128-row tile (two 64-token segments at
+  // 512 keys, 8 tiles: 9.5 us as tiles, 6.2 us as 16 items; 56 tiles of a
+  // 1.7K prompt 18.9 and 12.9 us).  Past one item per CU the chains queue up
+  // and the K/V reads, no longer shared by 128 rows, cost more than they save
+  // (192 tiles at 0.8K keys: 20.0 us, 20.2 us as 768 items; 344 tiles: 24.9
+  // and 42 us); nor do long units pay, which tiles cut finer (58 tiles of up
+  // to 28.9K keys: 93 us, 195 us as items).
+  if (!forced_width && o.q_tile_tokens == 0 && P.tile_rows == kTileRowsNarrow && G <= kTileRowsDecode &&
+      (int64_t)narrow_units.size() < kCUs) {
+    std::vector<Unit> items = make_units(kTileRowsDecode / G);
+    if ((int64_t)items.size() < kCUs) {
+      int64_t longest = 0, total_steps = 0;
+      for (const Unit& u : narrow_units) {
+        longest = std::max(longest, steps(u.kv_hi));
+        total_steps += steps(u.kv_hi);
+      }
+      const int64_t tile_chain = std::min(longest, std::max<int64_t>(kMinSplitSteps, total_steps / kCUs));
+      const int64_t item_chain =
+          std::min(longest, shortest_cut(items, kMinSplitKeysDecode, kWholeKeysDecode, kCUs) / kKvStep);
+      if (2 * item_chain <= 3 * tile_chain) {
+        P.item_rows = kTileRowsDecode;
+        P.tile_tokens = kTileRowsDecode / G;
+        narrow_units.clear();
+      }
+    }
   }
   const int32_t tile_tokens = P.tile_tokens;
   const int64_t slots_total = (int64_t)kCUs * (P.tile_rows == kTileRowsWide ? 1 : 2);
@@ -276,36 +324,36 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
 
   // 4. key splits decided by length alone: forced, or those of 32-row plans.
   // Other plans cut units where the workgroups' loads need it (step 6).
-  auto steps = [](int64_t keys) { return (keys + kKvStep - 1) / kKvStep; };
   const bool auto_split = o.kv_split_tokens == 0 && !(o.flags & MSA_PLAN_NO_AUTO_SPLIT);
-  const bool cut_to_fit = auto_split && P.tile_rows != kTileRowsDecode;
+  const bool cut_to_fit = auto_split && P.item_rows != kTileRowsDecode;
   int64_t split_keys = o.kv_split_tokens;  // 0: no split
-  if (auto_split && P.tile_rows == kTileRowsDecode && !units.empty() && (int64_t)units.size() <= slots_total) {
-    // 32-row tiles (decode-like, bound by K/V streaming; the four waves of
+  int64_t whole_keys = 0;  // units of up to this many keys are not split
+  if (auto_split && P.item_rows == kTileRowsDecode && !units.empty() && (int64_t)units.size() <= slots_total) {
+    // 32-row items (decode-like, bound by K/V streaming; the four waves of
     // a workgroup already split an item's keys): all pieces in one round
     // of the workgroup slots, the longest piece as short as possible, i.e.
     // the shortest 64-aligned piece length whose piece count fits the
     // slots (no split if the units alone exceed them)
-    auto pieces_at = [&](int64_t len) {
-      int64_t c = 0;
-      for (const Unit& u : units) c += (u.kv_hi + len - 1) / len;
-      return c;
-    };
-    int64_t longest = 0;
-    for (const Unit& u : units) longest = std::max<int64_t>(longest, u.kv_hi);
-    int64_t lo = kKvStep, hi = (longest + kKvStep - 1) / kKvStep * kKvStep;
-    while (lo < hi) {  // smallest length with pieces_at(length) <= slots
-      const int64_t mid = (lo / kKvStep + hi / kKvStep) / 2 * kKvStep;
-      if (pieces_at(mid) <= slots_total) hi = mid; else lo = mid + kKvStep;
+    split_keys = shortest_cut(units, kKvStep, 0, slots_total);
+    // Pieces below 1024 keys pay only while each has a CU to itself (8 heads
+    // at 8K keys: 16.1 us in pieces of 1024 keys, 12.9 of 512, 12.2 of 256;
+    // 58 units of up to 6.9K keys: 20.8 us in 228 pieces, 21.7 in 426), and
+    // not for units whose chain is no longer than the merge launch takes.
+    if (split_keys < kMinSplitKeys || P.tile_rows != kTileRowsDecode) {
+      whole_keys = kWholeKeysDecode;
+      split_keys = shortest_cut(units, kMinSplitKeysDecode, whole_keys, kCUs);
+      if (P.tile_rows == kTileRowsDecode) split_keys = std::min(split_keys, kMinSplitKeys);
+      int64_t longest = 0;
+      for (const Unit& u : units) longest = std::max<int64_t>(longest, u.kv_hi);
+      if (longest - split_keys < kMinSplitKeysDecode) split_keys = 0;
     }
-    split_keys = std::max<int64_t>(kMinSplitKeys, lo);
   }
   // A chunk is a run of key steps of one unit that is handed to workgroups
   // whole or, if cuttable, piece by piece.
   struct Piece {
     int32_t unit, lo, hi, wg;
   };
-  const double ov = P.tile_rows == kTileRowsDecode ? kItemStepsDecode : kItemSteps;
+  const double ov = P.item_rows == kTileRowsDecode ? kItemStepsDecode : kItemSteps;
   auto pcost = [&](const Piece& p) { return (double)steps(p.hi - p.lo) + ov; };
   std::vector<Piece> chunks;
   chunks.reserve(units.size());
@@ -320,7 +368,7 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
   for (size_t ui = 0; ui < units.size(); ++ui) {
     const Unit& u = units[ui];
     int64_t chunk = u.kv_hi;
-    if (split_keys > 0 && u.kv_hi > split_keys) {  // equal 64-aligned chunks, the last one takes the remainder
+    if (split_keys > 0 && u.kv_hi > std::max(split_keys, whole_keys)) {  // equal 64-aligned chunks, the last one takes the remainder
       const int64_t nsplit = (u.kv_hi + split_keys - 1) / split_keys;
       chunk = steps((u.kv_hi + nsplit - 1) / nsplit) * kKvStep;
     }
@@ -550,7 +598,7 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
     // waves whose 32 rows are all empty skip every step
     const double rows = (double)((w.nrows * G + 31) / 32 * 32);
     // 32-row tiles run 32-key half-steps, the others 64-key steps
-    const int64_t gran = P.tile_rows == kTileRowsDecode ? kKvStep / 2 : kKvStep;
+    const int64_t gran = P.item_rows == kTileRowsDecode ? kKvStep / 2 : kKvStep;
     P.tile_flops += 4.0 * d * rows * (double)((w.kv_hi - w.kv_lo + gran - 1) / gran * gran);
   }
   P.min_bytes = qo_bytes;

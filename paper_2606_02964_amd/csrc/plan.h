@@ -14,7 +14,8 @@ struct HostPlan {
   msa_shape shape{};
   int32_t group = 1;        // G = Hq / Hkv
   int32_t tile_rows = 0;    // rows per tile: kTileRowsDecode, kTileRowsNarrow or kTileRowsWide
-  int32_t tile_tokens = 0;  // query tokens per tile
+  int32_t item_rows = 0;    // rows per work item: tile_rows, or kTileRowsDecode in a 128-row plan of few tiles
+  int32_t tile_tokens = 0;  // query tokens per work item
   bool precise_weights = false;  // MSA_PLAN_PRECISE_WEIGHTS: hi + lo weights on every step
   int64_t total_q = 0;
   std::vector<int32_t> row_pos;   // [total_q] absolute position of each packed row

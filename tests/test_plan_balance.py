@@ -65,3 +65,26 @@ def test_short_units_are_not_cut():
     long = _descriptors([30000], [[(29000, 1000)]], 32, 8, 128)
     assert host_plan(msa, long).info()["num_merge"] > 0
     assert host_plan(msa, long, flags=msa.MSA_PLAN_NO_AUTO_SPLIT).info()["num_merge"] == 0
+
+
+@pytest.mark.parametrize("lens,segs,hq,hkv,d,items", [
+    ([512], [[(128, 64), (384, 64)]], 4, 4, 64, True),
+    ([1000, 300], [[(900, 100)], [(0, 5), (299, 1)]], 8, 2, 128, True),
+    ([700], [[(700 - 248, 248)]], 32, 8, 128, True),      # 31 x 8 items of 8 tokens
+    ([700], [[(700 - 249, 249)]], 32, 8, 128, False),     # 32 x 8: no longer fewer than CUs
+    ([6000], [[(5900, 60)]], 8, 2, 128, True),            # split, a CU for each piece
+    ([28861], [[(7215, 304), (28253, 608)]], 8, 2, 128, False),
+])
+def test_few_tiles_run_as_32_row_items(lens, segs, hq, hkv, d, items):
+    """128-row plans of few short tiles: items of up to 32 rows, one per CU at most."""
+    inst = _inst(lens, segs, hq, hkv, d)
+    G = hq // hkv
+    plan = host_plan(msa, inst)
+    info = plan.info()
+    row_pos, work, merge = msa.msa_plan_export(plan)
+    check_plan(inst, row_pos, work, merge, info, G)
+    assert info["tile_rows"] == 128
+    assert ((work[:, 3] * G).max() <= 32) == items
+    assert not items or len(work) <= 256
+    forced = host_plan(msa, inst, flags=msa.MSA_PLAN_TILE_ROWS_128)
+    assert (msa.msa_plan_export(forced)[1][:, 3] * G).max() > 32
