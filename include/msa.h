@@ -132,10 +132,10 @@ typedef struct msa_plan_opts {
  * on inputs whose scores make a few keys carry a row's weight, this moves
  * the output by up to 2^-8 * sum_j p_j |v_j| (p_j the normalised weights)
  * before its own bf16 rounding.  With this flag the weights hold to about
- * 2^-17, at the cost of a second P.V product on every step and no
- * software pipelining: 1.3 to 1.5 times the time of a call on plans with
- * prefill rows, about the same on decode-like plans (bound by streaming
- * K/V).  The plan is otherwise the same. */
+ * 2^-17, at the cost of a second P.V product on every step: 1.3 to 1.5
+ * times the time of a call on plans with prefill rows, about the same on
+ * decode-like plans (bound by streaming K/V).  The plan is otherwise the
+ * same. */
 #define MSA_PLAN_PRECISE_WEIGHTS 32
 
 /* Figures describing a plan. */

@@ -45,7 +45,7 @@
 // half-steps carry their weights as hi + lo terms, as above.
 // Both kernels also come in a precise-weights form (kPrecise, selected by
 // the plan): every step, or half-step, carries every row's weights as
-// hi + lo terms, and the main kernel then runs every step unpipelined.
+// hi + lo terms.
 // msa_merge: combines the per-split partials of a split tile by log-sum-exp.
 #include <hip/hip_runtime.h>
 
@@ -306,7 +306,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   constexpr int kQk = 2 * (D / 16);                   // QK MFMAs per step, ordered (kk, kt)
   constexpr int kPv = 4 * (D / 32);                   // PV MFMAs per step, ordered (ks, dt)
   constexpr int kElPerQk = 32 / kQk;                  // scores handled per QK MFMA
-  constexpr int kElPerPv = 32 / kPv;                  // scores handled per PV MFMA
+  constexpr int kElPerPv = 32 / kPv;                  // scores handled per V operand
   constexpr int kAhead = 3;                           // operand reads issued ahead of their MFMA
 
   // K operand of QK MFMA i of step s (register i of a lane: key row kt*32 + krow_m)
@@ -395,6 +395,31 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
         pack_bf16x2(sbuf[b][e >> 4][e & 15] - (float)h[0], sbuf[b][(e + 1) >> 4][(e + 1) & 15] - (float)h[1]);
     return own ? lo : 0u;
   };
+  // packed bf16 hi and lo terms of the weights e, e+1 held in sbuf[b]
+  auto hi_lo_pair = [&](int b, int e, uint32_t& hi, uint32_t& lo) {
+    hi = pack_bf16x2(sbuf[b][e >> 4][e & 15], sbuf[b][(e + 1) >> 4][(e + 1) & 15]);
+    lo = lo_pair(b, e, hi, true);
+  };
+  // largest score of a lane in sbuf[b]
+  auto step_max = [&](int b) {
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int e = 0; e < 32; ++e) mx = fmaxf(mx, sbuf[b][e >> 4][e & 15]);
+    return mx;
+  };
+  // moves the reference of the rows whose max (mx: a lane's) exceeds it by
+  // more than 2^8 and rescales their sums; whether any did (wave-uniform)
+  auto move_reference = [&](float mx) -> bool {
+    const float m_blk = pair_max(mx) * c;
+    const bool grow = m_blk > m_ref + kRescaleLog2;
+    if (!__any(grow)) return false;
+    const float alpha = grow ? __builtin_amdgcn_exp2f(m_ref - m_blk) : 1.0f;
+    m_ref = grow ? m_blk : m_ref;
+    l_run *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) oacc[dt] *= alpha;
+    return true;
+  };
   // The row max is only taken when the weights of a step may have outgrown
   // the reference: a lane's step sum reached 2^7, or the row has no
   // reference yet.  A row whose max exceeds the reference by more than 2^8
@@ -404,19 +429,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   // (reweigh recomputes the step's weights and their sum ls.)
   auto settle = [&](int b, float ls, auto&& reweigh) {
     if (__any(!(ls < kSettleSum) || m_ref == -__builtin_inff())) {  // wave-uniform
-      float mx = -__builtin_inff();
-#pragma unroll
-      for (int e = 0; e < 32; ++e) mx = fmaxf(mx, sbuf[b][e >> 4][e & 15]);
-      const float m_blk = pair_max(mx) * c;
-      const bool grow = m_blk > m_ref + kRescaleLog2;
-      if (__any(grow)) {
-        const float alpha = grow ? __builtin_amdgcn_exp2f(m_ref - m_blk) : 1.0f;
-        m_ref = grow ? m_blk : m_ref;
-        l_run *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt) oacc[dt] *= alpha;
-        reweigh();
-      }
+      if (move_reference(step_max(b))) reweigh();
     }
   };
 
@@ -427,6 +440,13 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   // The source order is fixed with scheduling fences.  j has the parity of
   // B (the paired loop starts at step 0), so step j+1's K sits in ring stage
   // 1-B and step j's V in stage B.
+  // With precise weights the fp32 weights stay in sbuf[B] in place of the
+  // scores, so the reference must be settled before them: block 2 takes the
+  // row max of step j+1 beside its MFMAs, and every V operand it reads feeds
+  // the hi and the lo product (the lo terms of the next 16 keys are formed
+  // meanwhile).  Against unpipelined steps with a second pass over V: the
+  // 8 x 8192 workload 2042 -> 1947 us, 32-token segments at 4K 1510 -> 1408 us;
+  // at d = 64, where vector instructions bound the step, 299 -> 298 us.
   auto fused = [&](auto bsel, auto&& addresses) {
     constexpr int B = decltype(bsel)::value, NB = 1 - B;
     const float nm = m_ref == -__builtin_inff() ? 0.0f : -m_ref;
@@ -451,15 +471,27 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
         const int e = i * kElPerQk + u;
         const float w0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sbuf[B][e >> 4][e & 15], c, nm));
         const float w1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sbuf[B][(e + 1) >> 4][(e + 1) & 15], c, nm));
-        pk[e >> 1] = pack_bf16x2(w0, w1);
+        if constexpr (kPrecise) {
+          sbuf[B][e >> 4][e & 15] = w0;
+          sbuf[B][(e + 1) >> 4][(e + 1) & 15] = w1;
+        } else {
+          pk[e >> 1] = pack_bf16x2(w0, w1);
+        }
         ls += w0 + w1;
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    settle(B, ls, [&]() { weights_plain(B, pk, ls); });
+    if constexpr (!kPrecise) settle(B, ls, [&]() { weights_plain(B, pk, ls); });
     l_run += ls;
     // block 2
     bf16x8 va[kPv];
+    constexpr int kPairs = 4 / (D / 32);  // hi and lo pairs of the next 16 keys formed per V operand
+    uint32_t pl[16];
+    float mx = -__builtin_inff();
+    if constexpr (kPrecise) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) hi_lo_pair(B, 2 * u, pk[u], pl[u]);
+    }
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) va[a] = vread_c(std::integral_constant<int, B>{}, a);
 #pragma unroll
@@ -467,11 +499,23 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
       if (i + kAhead < kPv) va[i + kAhead] = vread_c(std::integral_constant<int, B>{}, i + kAhead);
       const int ks = i / (D / 32), dt = i % (D / 32);
       // P sub-step ks = keys 16*ks + hl*8 .. +8 = packed weights 4*ks .. 4*ks+3
+      // (precise: the pairs of sub-step ks + 1 are formed beside the MFMAs of ks)
       const bf16x8 pb = __builtin_bit_cast(bf16x8, make_uint4(pk[4 * ks], pk[4 * ks + 1], pk[4 * ks + 2], pk[4 * ks + 3]));
       oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pb, oacc[dt], 0, 0, 0);
+      if constexpr (kPrecise) {
+        const bf16x8 pc = __builtin_bit_cast(bf16x8, make_uint4(pl[4 * ks], pl[4 * ks + 1], pl[4 * ks + 2], pl[4 * ks + 3]));
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pc, oacc[dt], 0, 0, 0);
+        if (ks < 3) {
+#pragma unroll
+          for (int u = 4 * (ks + 1) + dt * kPairs; u < 4 * (ks + 1) + (dt + 1) * kPairs; ++u) hi_lo_pair(B, 2 * u, pk[u], pl[u]);
+        }
+#pragma unroll
+        for (int e = i * kElPerPv; e < (i + 1) * kElPerPv; ++e) mx = fmaxf(mx, sbuf[NB][e >> 4][e & 15]);
+      }
       if (i == 0) addresses();
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (kPrecise) move_reference(mx);
   };
 
   // Step s's K sits in K buffer s % 2 and its V in V buffer s % 2; in
@@ -500,6 +544,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   if (nw > 0) {
     qk_plain(0, 0);
     if (need_mask(0)) mask_plain(0, 0);
+    if constexpr (kPrecise) move_reference(step_max(0));
   }
   lds_barrier();  // every wave is done with K_0 before K_2 replaces it
 
@@ -514,10 +559,9 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     wait_dma<0>();
     lds_barrier();
   };
-  // (with precise weights every step runs unpipelined, below)
   int j = 0;
   const int whole = (w.kv_hi - w.kv_lo) / kKvStep;  // steps without a missing block
-  for (; !kPrecise && j + 2 < nw && !need_mask(j + 2); j += 2) {
+  for (; j + 2 < nw && !need_mask(j + 2); j += 2) {
     copy_whole(j);  // step j+2 is not masked, hence whole
     fused(std::integral_constant<int, 0>{}, [&]() { next_pages(j + 3); });
     tail();
@@ -533,7 +577,34 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   // On a masked step (split: the diagonal step of some row of the wave) the
   // rows whose diagonal step it is also enter their weights' bf16 lo terms
   // (other rows: zeros), in a second PV pass after the usual one on pk.
-  // With precise weights every step is split and every row enters them.
+  // With precise weights every row enters them on every step, V operand by V
+  // operand as in the pipelined loop (the same sums in the same order).
+  auto plain_precise = [&](int jj) {
+    weights_inplace(0);
+    float ls = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 32; e += 2) ls += sbuf[0][e >> 4][e & 15] + sbuf[0][(e + 1) >> 4][(e + 1) & 15];
+    l_run += ls;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      uint32_t ph[4], pl[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) hi_lo_pair(0, 8 * ks + 2 * u, ph[u], pl[u]);
+      const bf16x8 pb = __builtin_bit_cast(bf16x8, make_uint4(ph[0], ph[1], ph[2], ph[3]));
+      const bf16x8 pc = __builtin_bit_cast(bf16x8, make_uint4(pl[0], pl[1], pl[2], pl[3]));
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) {
+        const bf16x8 a = vread(jj, ks * (D / 32) + dt);
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb, oacc[dt], 0, 0, 0);
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pc, oacc[dt], 0, 0, 0);
+      }
+    }
+    if (jj + 1 < nw) {
+      qk_plain(0, jj + 1);
+      if (need_mask(jj + 1)) mask_plain(0, jj + 1);
+      move_reference(step_max(0));
+    }
+  };
   auto plain = [&](int jj, bool split) {
     uint32_t pk[16];
     float ls;
@@ -555,7 +626,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
         const int ks = i / (D / 32), dt = i % (D / 32);
         uint32_t pl[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) pl[u] = lo_pair(0, 8 * ks + 2 * u, pk[4 * ks + u], own || kPrecise);
+        for (int u = 0; u < 4; ++u) pl[u] = lo_pair(0, 8 * ks + 2 * u, pk[4 * ks + u], own);
         const bf16x8 pc = __builtin_bit_cast(bf16x8, make_uint4(pl[0], pl[1], pl[2], pl[3]));
         oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vread(jj, i), pc, oacc[dt], 0, 0, 0);
       }
@@ -569,7 +640,10 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     copy_any(page, j + 2, kBoth ? vpage : page, j + 1);
     move_ids(j + 3);
     next_pages(j + 3);
-    if (j < nw) plain(j, kPrecise || need_mask(j));
+    if (j < nw) {
+      if constexpr (kPrecise) plain_precise(j);
+      else plain(j, need_mask(j));
+    }
     tail();
   }
 

@@ -13,16 +13,17 @@ import workloads
 from gpu_helpers import DeviceInstance, check_o, run
 
 
+@pytest.mark.parametrize("precise", [0, msa.MSA_PLAN_PRECISE_WEIGHTS])
 @pytest.mark.parametrize("tile", [msa.MSA_PLAN_TILE_ROWS_32, msa.MSA_PLAN_TILE_ROWS_128,
                                   msa.MSA_PLAN_TILE_ROWS_256])
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (3, 1, 64)])
 @pytest.mark.parametrize("L", [64 * 3, 64 * 3 + 1, 64 * 64 - 1, 64 * 64, 64 * 64 + 33, 64 * 65 + 16, 64 * 67,
                                64 * 128 + 49, 64 * 131])
-def test_id_windows_and_last_steps(oracle_lib, L, hq, hkv, d, tile):
+def test_id_windows_and_last_steps(oracle_lib, L, hq, hkv, d, tile, precise):
     """An unsplit item of L keys: rows at the end of the context, and a few in
     the middle that share their tile."""
     mid = L // 2
     inst = workloads.make_layout(500 + L, [L], [[(mid, 5), (L - 20, 20)]], hq, hkv, d, keep_logical=False)
     ro, rl = oracle_lib.forward(inst)
-    o, lse, _ = run(DeviceInstance(inst), flags=tile | msa.MSA_PLAN_NO_AUTO_SPLIT)
+    o, lse, _ = run(DeviceInstance(inst), flags=tile | precise | msa.MSA_PLAN_NO_AUTO_SPLIT)
     check_o(o.float().cpu().numpy(), ro, lse.cpu().numpy(), rl)
