@@ -220,36 +220,34 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   auto vbuf = [&](int s) -> char* {
     return smem + __builtin_amdgcn_readfirstlane(2 * T::kBytesK + (s & 1) * T::kBytesV);
   };
-  // A step has 8 pages: the K and the V page of each of its 4 blocks.  With 4
-  // waves each copies both pages of its block slot; with 8, waves 0-3 copy the
-  // K pages and waves 4-7 the V pages.  Iteration j copies the K of step j+2
-  // and the V of step j+1, so the id read for a K page serves the V page of
-  // the next iteration.  A block at or past kv_hi is not read; its V page is
-  // zero-filled instead (its K page keeps old values: those keys are masked by
-  // selection, so never meet arithmetic).
-  constexpr bool kBoth = W == 4;  // a wave copies the K and the V page of its slot
-  const bool copies_k = kBoth || wave < 4, copies_v = kBoth || wave >= 4;
-  const char* const pbase = copies_k ? kbase : vbase;  // of the wave's pages (kBoth: of K)
-  const int64_t psb = copies_k ? ksb : vsb;
-  const char *page, *vpage;   // pages of the next copies
+  // A step has 8 pages: the K and the V page of each of its 4 blocks; a
+  // copying wave copies both pages of its block slot.  With 8 waves only waves
+  // 4-7 copy, one on each SIMD, while waves 0-3 go straight to their MFMAs:
+  // issuing a wave's copies takes it 40-80 cycles each, in which a SIMD whose
+  // two waves both copy issues nothing else (338 of a step's 3360 cycles; with
+  // four copying waves the 8 x 8192 workload takes 1389 us, not 1404, and
+  // 2 x 32768 7628 us, not 7700).
+  // Iteration j copies the K of step j+2 and the V of step j+1, so the id read
+  // for a K page serves the V page of the next iteration.  A block at or past
+  // kv_hi is not read; its V page is zero-filled instead (its K page keeps old
+  // values: those keys are masked by selection, so never meet arithmetic).
+  const bool copier = W == 4 || wave >= 4;  // wave-uniform
+  const char *kpage, *vpage;  // pages of the next copies
   int32_t id_cur = 0;
   // Reads the ids of K step s and V step s - 1 and takes their page
   // addresses; called for s = 0, 1, 2, ... in turn, one iteration before the
   // copies, where the address arithmetic runs beside MFMAs.  (Taken at the
   // start of the iteration, with the range checks of both pages, it held up
   // every wave before its first MFMA: a step of a lone workgroup took 1.07 us
-  // with 4 waves and 0.89 us with 8, d = 128, and now takes 0.90 and 0.82 us.)
+  // with 4 waves, d = 128, and now takes 0.90 us.)
   auto next_pages = [&](int s) __attribute__((always_inline)) {
     const int32_t id_prev = id_cur;
     id_cur = __builtin_amdgcn_readlane(idv, s & 63);
     // pinned to scalar registers here: left to itself the compiler moves the
     // products to the copies and spills 130 vector registers
-    page = pbase + (int64_t)(copies_k ? id_cur : id_prev) * psb;
-    asm volatile("" : "+s"(page));
-    if constexpr (kBoth) {
-      vpage = vbase + (int64_t)id_prev * vsb;
-      asm volatile("" : "+s"(vpage));
-    }
+    kpage = kbase + (int64_t)id_cur * ksb;
+    vpage = vbase + (int64_t)id_prev * vsb;
+    asm volatile("" : "+s"(kpage), "+s"(vpage));
   };
   // before next_pages(s) at multiples of 64: the next 64 ids move in
   auto move_ids = [&](int s) __attribute__((always_inline)) {
@@ -270,20 +268,16 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   };
   // copies of iteration j, both steps whole
   auto copy_whole = [&](int j) __attribute__((always_inline)) {
-    if constexpr (kBoth) {
-      copy_k(page, j + 2);
-      copy_v(vpage, j + 1);
-    } else if (copies_k) {
-      copy_k(page, j + 2);
-    } else {
-      copy_v(page, j + 1);
-    }
+    if (!copier) return;
+    copy_k(kpage, j + 2);
+    copy_v(vpage, j + 1);
   };
   // K of step sk and V of step sv where either may end inside the step or lie past the end
   auto copy_any = [&](const char* ksrc, int sk, const char* vsrc, int sv) {
+    if (!copier) return;
     const int kb = w.kv_lo + bslot * kBlockSize;
-    if (copies_k && kb + sk * kKvStep < w.kv_hi) copy_k(ksrc, sk);
-    if (copies_v && sv < n) {
+    if (kb + sk * kKvStep < w.kv_hi) copy_k(ksrc, sk);
+    if (sv < n) {
       if (kb + sv * kKvStep < w.kv_hi) {
         copy_v(vsrc, sv);
       } else {
@@ -526,7 +520,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   next_pages(0);
   copy_any(kbase + (int64_t)id_cur * ksb, 0, vbase + (int64_t)id_cur * vsb, 0);
   next_pages(1);
-  if (copies_k) copy_any(page, 1, vbase, n);
+  copy_any(kpage, 1, vbase, n);
   next_pages(2);
   // wave-wide smallest and largest causal limit: a tile's rows are in
   // ascending position, so those of its first and last row
@@ -566,7 +560,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     fused(std::integral_constant<int, 0>{}, [&]() { next_pages(j + 3); });
     tail();
     if (j + 3 < whole) copy_whole(j + 1);
-    else copy_any(page, j + 3, kBoth ? vpage : page, j + 2);
+    else copy_any(kpage, j + 3, vpage, j + 2);
     move_ids(j + 4);
     fused(std::integral_constant<int, 1>{}, [&]() { next_pages(j + 4); });
     tail();
@@ -637,7 +631,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     }
   };
   for (; j < n; ++j) {
-    copy_any(page, j + 2, kBoth ? vpage : page, j + 1);
+    copy_any(kpage, j + 2, vpage, j + 1);
     move_ids(j + 3);
     next_pages(j + 3);
     if (j < nw) {
