@@ -146,7 +146,7 @@ __device__ __forceinline__ int div_group(int r, const AttnParams& p) {
 // (2 steps).  Every wave leaves through the barrier that ends the item's
 // last step before its epilogue (registers only), so the next item may
 // refill the rings at once.
-template <int D, int W, bool kPrecise>
+template <int D, int W, bool kPrecise, bool kHelp>
 __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w, char* smem) {
   using T = Tile<D>;
   constexpr int kRows = 32 * W;  // tile rows
@@ -221,8 +221,9 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     return smem + __builtin_amdgcn_readfirstlane(2 * T::kBytesK + (s & 1) * T::kBytesV);
   };
   // A step has 8 pages: the K and the V page of each of its 4 blocks; a
-  // copying wave copies both pages of its block slot.  With 8 waves only waves
-  // 4-7 copy, one on each SIMD, while waves 0-3 go straight to their MFMAs:
+  // copying wave copies both pages of its block slot.  With 8 waves (256-row
+  // tiles, and the helpers of kHelp) only waves 4-7 copy, one on each SIMD,
+  // while waves 0-3 go straight to their MFMAs:
   // issuing a wave's copies takes it 40-80 cycles each, in which a SIMD whose
   // two waves both copy issues nothing else (338 of a step's 3360 cycles; with
   // four copying waves the 8 x 8192 workload takes 1389 us, not 1404, and
@@ -231,7 +232,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   // for a K page serves the V page of the next iteration.  A block at or past
   // kv_hi is not read; its V page is zero-filled instead (its K page keeps old
   // values: those keys are masked by selection, so never meet arithmetic).
-  const bool copier = W == 4 || wave >= 4;  // wave-uniform
+  const bool copier = wave >= 4 || (W == 4 && !kHelp);  // wave-uniform
   const char *kpage, *vpage;  // pages of the next copies
   int32_t id_cur = 0;
   // Reads the ids of K step s and V step s - 1 and takes their page
@@ -687,7 +688,25 @@ __global__ __launch_bounds__(64 * W, 2) void msa_attn_kernel(AttnParams p) {
   const WgHead head = p.heads[blockIdx.x];
   WorkItem w = head.first;
   for (int it = head.rest;; w = p.work[it++]) {
-    attn_item<D, W, kPrecise>(p, w, smem);
+    attn_item<D, W, kPrecise, false>(p, w, smem);
+    if (it >= head.end) break;
+  }
+}
+
+// The same for 128-row tiles in a launch of no more workgroups than CUs: four
+// further waves that only copy.  Alone on its CU, a 4-wave workgroup issues its
+// copies (402 of a step's 2430 cycles) with nothing to run beside them; the
+// helpers need the registers of a second workgroup, which such a launch does
+// not place.  Suffix recompute at 1K, 144 tiles: 22.3 -> 20.4 us; 192 tiles at
+// 0.8K keys 20.4 -> 18.7 us.
+template <int D, bool kPrecise>
+__global__ __launch_bounds__(512, 2) void msa_helped_kernel(AttnParams p) {
+  using T = Tile<D>;
+  __shared__ __attribute__((aligned(1024))) char smem[2 * T::kBytesK + 2 * T::kBytesV];
+  const WgHead head = p.heads[blockIdx.x];
+  WorkItem w = head.first;
+  for (int it = head.rest;; w = p.work[it++]) {
+    attn_item<D, 4, kPrecise, true>(p, w, smem);
     if (it >= head.end) break;
   }
 }
@@ -1048,7 +1067,11 @@ __global__ __launch_bounds__(256) void msa_merge_kernel(MergeParams p) {
 // default kernels carry no test of the flag.
 template <bool kPrecise>
 int launch_attn_form(const AttnParams& p, int head_dim, int item_rows, int num_wg, hipStream_t s) {
-  if (head_dim == 128 && item_rows == kTileRowsNarrow)
+  if (item_rows == kTileRowsNarrow && num_wg <= kCUs && head_dim == 128)
+    hipLaunchKernelGGL((msa_helped_kernel<128, kPrecise>), dim3(num_wg), dim3(512), 0, s, p);
+  else if (item_rows == kTileRowsNarrow && num_wg <= kCUs && head_dim == 64)
+    hipLaunchKernelGGL((msa_helped_kernel<64, kPrecise>), dim3(num_wg), dim3(512), 0, s, p);
+  else if (head_dim == 128 && item_rows == kTileRowsNarrow)
     hipLaunchKernelGGL((msa_attn_kernel<128, 4, kPrecise>), dim3(num_wg), dim3(256), 0, s, p);
   else if (head_dim == 128 && item_rows == kTileRowsWide)
     hipLaunchKernelGGL((msa_attn_kernel<128, 8, kPrecise>), dim3(num_wg), dim3(512), 0, s, p);

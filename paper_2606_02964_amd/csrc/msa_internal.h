@@ -24,6 +24,7 @@ constexpr int kTileRowsWide = 256;
 constexpr int kTileRowsDecode = 32;
 constexpr int kKvStep = 64;      // keys per main-loop iteration (4 blocks of 16)
 constexpr int kBlockSize = 16;
+constexpr int kCUs = 256;        // compute units, 32 on each of the 8 XCDs
 
 struct WorkItem {
   int32_t seq;

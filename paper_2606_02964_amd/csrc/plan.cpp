@@ -46,7 +46,6 @@ namespace msa {
 namespace {
 
 constexpr int kXcds = 8;
-constexpr int kCUs = 256;
 constexpr int64_t kWideMinTiles = 1024;  // narrow tiles from which wide tiles pay
 // 64-key steps per workgroup slot of the narrow tiling from which wide tiles
 // pay: shorter plans gain more from two workgroups per CU (one's start-up

@@ -27,3 +27,20 @@ def test_id_windows_and_last_steps(oracle_lib, L, hq, hkv, d, tile, precise):
     ro, rl = oracle_lib.forward(inst)
     o, lse, _ = run(DeviceInstance(inst), flags=tile | precise | msa.MSA_PLAN_NO_AUTO_SPLIT)
     check_o(o.float().cpu().numpy(), ro, lse.cpu().numpy(), rl)
+
+
+@pytest.mark.parametrize("seqs", [32, 33])
+def test_workgroups_at_and_past_one_per_cu(oracle_lib, seqs):
+    """128-row tiles in 256 workgroups (one per CU, with copying helper waves)
+    and in 264 (without): every row with the oracle, and bit for bit with
+    256-row tiles."""
+    L = 64 * 66 + 21
+    segs = [[(L - 3, 3)] if b % 4 else [(L - 60, 2), (L - 30, 30)] for b in range(seqs)]
+    inst = workloads.make_layout(91, [L] * seqs, segs, 16, 8, 64, keep_logical=False)
+    ro, rl = oracle_lib.forward(inst)
+    flags = msa.MSA_PLAN_TILE_ROWS_128 | msa.MSA_PLAN_NO_AUTO_SPLIT
+    o, lse, plan = run(DeviceInstance(inst), flags=flags)
+    assert (plan.info()["num_workgroups"] <= 256) == (seqs == 32)
+    check_o(o.float().cpu().numpy(), ro, lse.cpu().numpy(), rl)
+    o2, _, wide = run(DeviceInstance(inst), flags=msa.MSA_PLAN_TILE_ROWS_256 | msa.MSA_PLAN_NO_AUTO_SPLIT)
+    assert wide.info()["tile_rows"] == 256 and torch.equal(o2.view(torch.int16), o.view(torch.int16))
