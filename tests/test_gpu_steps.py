@@ -17,7 +17,7 @@ from gpu_helpers import DeviceInstance, check_o, run
 @pytest.mark.parametrize("tile", [msa.MSA_PLAN_TILE_ROWS_32, msa.MSA_PLAN_TILE_ROWS_128,
                                   msa.MSA_PLAN_TILE_ROWS_256])
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (3, 1, 64)])
-@pytest.mark.parametrize("L", [64 * 3, 64 * 3 + 1, 64 * 64 - 1, 64 * 64, 64 * 64 + 33, 64 * 65 + 16, 64 * 67,
+@pytest.mark.parametrize("L", [64 * 2, 64 * 3, 64 * 3 + 1, 64 * 4 + 5, 64 * 5, 64 * 64 - 1, 64 * 64, 64 * 64 + 33, 64 * 65 + 16, 64 * 67,
                                64 * 128 + 49, 64 * 131])
 def test_id_windows_and_last_steps(oracle_lib, L, hq, hkv, d, tile, precise):
     """An unsplit item of L keys: rows at the end of the context, and a few in
