@@ -114,7 +114,7 @@ typedef struct msa_plan_opts {
  *     (decode-like plans: the four waves of a workgroup split the tile's
  *     keys and read K and V straight into registers, two workgroups per CU);
  *   - 256-row tiles (one workgroup per CU; each K/V step is loaded once for
- *     twice the rows) when the plan has many tiles and a long run of key
+ *     twice the rows) when the plan has full tiles and a long run of key
  *     steps per workgroup slot;
  *   - else 128-row tiles (two workgroups per CU: one's start-up and tail
  *     overlap the other's work).  When such a plan has few short tiles, its

@@ -11,7 +11,7 @@
 //      across segment gaps as long as the keys masked for the earlier rows
 //      stay a small fraction of the tile's work.  tile_rows is 256 (one
 //      workgroup per CU, each K/V step loaded once for 256 rows) when the
-//      128-row tiling has many tiles and a long run of key steps per
+//      128-row tiling has full tiles and a long run of key steps per
 //      workgroup slot, else 128 (two workgroups per CU: one's start-up and
 //      tail overlap the other's work, and decode-heavy plans keep more key
 //      streams in flight); it is 32 when no 128-row tile would hold more
@@ -46,12 +46,19 @@ namespace msa {
 namespace {
 
 constexpr int kXcds = 8;
-constexpr int64_t kWideMinTiles = 1024;  // narrow tiles from which wide tiles pay
 // 64-key steps per workgroup slot of the narrow tiling from which wide tiles
-// pay: shorter plans gain more from two workgroups per CU (one's start-up
-// and tail overlap the other's work) than from loading each K/V step once
-// for 256 rows (measured crossover about 400 steps per slot)
-constexpr double kWideMinStepsPerSlot = 384.0;
+// pay: shorter plans gain more from two workgroups per CU (one's start-up and
+// tail overlap the other's work) than from loading each K/V step once for 256
+// rows.  Narrow against wide, us: head_dim 128, 75 steps 164 / 173, 109 steps
+// 231 / 224, 200 steps 427 / 419, 290 steps 566 / 541; head_dim 64, whose steps
+// are half as long, 160 steps 146 / 151, 185 steps 201 / 202.
+constexpr double kWideMinStepsPerSlot = 96.0;
+constexpr double kWideMinStepsPerSlot64 = 384.0;
+constexpr int64_t kWideMinTiles64 = 1024;  // narrow tiles, head_dim 64
+// ... and the share of the key steps' rows that hold queries: a decode row
+// takes a whole workgroup's step however wide (45 of 60 sequences decoding:
+// fill 0.82 1296 / 1313, 0.57 566 / 621; 24 of 32: 0.94 1645 / 1605)
+constexpr double kWideMinFill = 0.9;
 constexpr double kWasteFrac = 0.125;     // masked keys allowed per tile, relative
 constexpr int64_t kMinSplitKeys = 1024;  // never split below this many keys
 constexpr int64_t kMinSplitSteps = kMinSplitKeys / kKvStep;
@@ -219,7 +226,7 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
 
   // tile width: forced by a flag, else 32 rows when no 128-row tile would
   // hold more than 32 rows (decode-like plans), wide when the narrow tiling
-  // has many tiles and enough work per workgroup slot (G > 128 needs wide
+  // has full tiles and enough work per workgroup slot (G > 128 needs wide
   // tiles), else narrow
   const int32_t narrow_tokens = G <= kTileRowsNarrow ? kTileRowsNarrow / G : 0;
   std::vector<Unit> narrow_units;
@@ -234,15 +241,20 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
         rows = kTileRowsWide;
       } else {
         narrow_units = make_units(narrow_tokens);
-        double steps = 0;
+        double steps = 0, row_steps = 0;
         int64_t max_rows = 0;
         for (const Unit& u : narrow_units) {
-          steps += (double)((u.kv_hi + kKvStep - 1) / kKvStep);
+          const double st = (double)((u.kv_hi + kKvStep - 1) / kKvStep);
+          steps += st;
+          row_steps += st * u.nrows;
           max_rows = std::max<int64_t>(max_rows, (int64_t)u.nrows * G);
         }
+        const bool d64 = s.head_dim == 64;
         if (!narrow_units.empty() && max_rows <= kTileRowsDecode)
           rows = kTileRowsDecode;
-        else if ((int64_t)narrow_units.size() >= kWideMinTiles && steps >= kWideMinStepsPerSlot * 2.0 * kCUs)
+        else if (steps >= (d64 ? kWideMinStepsPerSlot64 : kWideMinStepsPerSlot) * 2.0 * kCUs &&
+                 row_steps >= kWideMinFill * steps * narrow_tokens &&
+                 (!d64 || (int64_t)narrow_units.size() >= kWideMinTiles64))
           rows = kTileRowsWide;
       }
     }
@@ -344,7 +356,9 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
       if (P.tile_rows == kTileRowsDecode) split_keys = std::min(split_keys, kMinSplitKeys);
       int64_t longest = 0;
       for (const Unit& u : units) longest = std::max<int64_t>(longest, u.kv_hi);
-      if (longest - split_keys < kMinSplitKeysDecode) split_keys = 0;
+      // (a merge launch takes as long as a chain of 500 keys: 216 items of up to
+      // 1.7K keys 13.8 us in pieces of up to 1408, 12.9 whole)
+      if (longest - split_keys < 2 * kMinSplitKeysDecode) split_keys = 0;
     }
   }
   // A chunk is a run of key steps of one unit that is handed to workgroups

@@ -88,3 +88,18 @@ def test_few_tiles_run_as_32_row_items(lens, segs, hq, hkv, d, items):
     assert not items or len(work) <= 256
     forced = host_plan(msa, inst, flags=msa.MSA_PLAN_TILE_ROWS_128)
     assert (msa.msa_plan_export(forced)[1][:, 3] * G).max() > 32
+
+
+@pytest.mark.parametrize("lens,segs,hq,hkv,d,rows", [
+    ([10240], [[(0, 5056), (10112, 128)]], 32, 8, 128, 256),   # 109 key steps per workgroup slot
+    ([8000], [[(0, 3850), (7700, 300)]], 32, 8, 128, 128),     # 75
+    ([30000], [[(7500, 300), (29400, 600)]], 32, 8, 128, 256),  # few tiles, each long
+    ([6468, 6431], None, 16, 16, 64, 128),                      # 160 of the shorter 64-wide steps
+    ([16000] * 8 + [12000] * 40, [[(15000, 1000)]] * 8 + [[(11999, 1)]] * 40, 32, 8, 128, 128),  # much decoding
+    ([16000] * 8 + [12000] * 4, [[(15000, 1000)]] * 8 + [[(11999, 1)]] * 4, 32, 8, 128, 256),    # little
+])
+def test_tile_width_by_steps_and_fill(lens, segs, hq, hkv, d, rows):
+    inst = _inst(lens, segs or [[(0, n)] for n in lens], hq, hkv, d)
+    plan = host_plan(msa, inst)
+    check_plan(inst, *msa.msa_plan_export(plan), plan.info(), hq // hkv)
+    assert plan.info()["tile_rows"] == rows
