@@ -10,7 +10,7 @@
 
 namespace msa {
 
-// One workgroup of the append: the rows of one segment that fall into one
+// One slice of the append: the rows of one segment that fall into one
 // cache block (consecutive rows row0 .. row0+n-1 at positions pos0 .. pos0+n-1,
 // 1 <= n <= 16, all inside block pos0 / 16 of sequence seq).
 struct AppendItem {
@@ -34,6 +34,7 @@ struct AppendParams {
   int32_t num_kv_heads;
   int32_t max_blocks;
   int32_t num_blocks;
+  int32_t head_groups;  // workgroups that share a slice's heads (set by launch_kv_append)
 };
 
 // Returns a hipError_t value as int.

@@ -1,9 +1,9 @@
 // append.hip -- gfx950 kernel that writes the fresh K/V of the packed query
 // rows into their paged cache slots.
 //
-// One workgroup (256 threads) takes one slice: the n <= 16 consecutive rows
-// of one segment that land in one cache block (the planner cuts every segment
-// at block boundaries), for every KV head, eight heads per pass:
+// One workgroup (256 threads) takes two KV heads of one slice: the n <= 16
+// consecutive rows of one segment that land in one cache block (the planner
+// cuts every segment at block boundaries):
 //   * K blocks are token-major, so each (row, head) is one contiguous d-vector
 //     in both the source and the cache: 16-byte loads and stores, 16 lanes per
 //     row (256 contiguous bytes for d = 128).
@@ -15,6 +15,14 @@
 //     consecutive tokens of one channel.
 // A slice whose block-table entry is outside [0, num_blocks) is not written.
 // The kernel is bound by HBM: it reads and writes each fresh K/V byte once.
+// A slice's heads are spread over workgroups because one workgroup of all 8
+// heads runs its reads, its LDS transpose and its stores one after the other,
+// in 35 KB of LDS that leave room for four per CU (20480 rows, 8 heads, d = 128:
+// 1280 workgroups for 1024 places).  168 MB in 40.1 us with 8 heads a
+// workgroup, 37.8 with 4, 35.6 with 2 (4.7 TB/s; a device copy reaches 4.9),
+// 34.6 with 1; 128 decode rows with their attention 299.4, 299.3, 298.9 and
+// 300.0 us, hence 2.  (Issuing all of a thread's loads before its stores,
+// with two lanes to a V channel, took 49 us at 2 heads.)
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -24,7 +32,7 @@
 namespace msa {
 namespace {
 
-constexpr int kHeadsPerPass = 8;
+constexpr int kHeadsPerPass = 2;  // KV heads a workgroup takes at a time
 
 template <int D>
 __global__ __launch_bounds__(256) void msa_kv_append_kernel(AppendParams p) {
@@ -37,7 +45,9 @@ __global__ __launch_bounds__(256) void msa_kv_append_kernel(AppendParams p) {
   uint16_t* __restrict__ k_cache = p.k_cache;
   uint16_t* __restrict__ v_cache = p.v_cache;
 
-  const AppendItem it = p.items[blockIdx.x];
+  const uint32_t item = blockIdx.x / (uint32_t)p.head_groups;
+  const int group = (int)(blockIdx.x - item * (uint32_t)p.head_groups);
+  const AppendItem it = p.items[item];
   const int32_t blk = p.block_table[(int64_t)it.seq * p.max_blocks + it.pos0 / 16];
   if (blk < 0 || blk >= p.num_blocks) return;  // uniform over the workgroup
   const int off0 = it.pos0 % 16;                // slice = tokens off0 .. off0+n-1 of the block
@@ -46,7 +56,7 @@ __global__ __launch_bounds__(256) void msa_kv_append_kernel(AppendParams p) {
   const int64_t kbase = (int64_t)blk * p.k_sb;
   const int64_t vbase = (int64_t)blk * p.v_sb;
 
-  for (int g0 = 0; g0 < p.num_kv_heads; g0 += kHeadsPerPass) {
+  for (int g0 = group * kHeadsPerPass; g0 < p.num_kv_heads; g0 += p.head_groups * kHeadsPerPass) {
     const int ng = p.num_kv_heads - g0 < kHeadsPerPass ? p.num_kv_heads - g0 : kHeadsPerPass;
     // K straight to the cache; V rows into LDS (slice row i at LDS row off0 + i).
     for (int idx = tid; idx < ng * n * kChunks; idx += 256) {
@@ -94,13 +104,20 @@ __global__ __launch_bounds__(256) void msa_kv_append_kernel(AppendParams p) {
 
 }  // namespace
 
-int launch_kv_append(const AppendParams& p, int head_dim, int num_items, void* stream) {
+int launch_kv_append(const AppendParams& params, int head_dim, int num_items, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (num_items <= 0) return 0;
+  AppendParams p = params;
+  // a workgroup per (slice, heads of a pass); fewer, each looping over its
+  // heads, where the grid would pass 2^23 workgroups
+  const int passes = p.num_kv_heads / kHeadsPerPass + (p.num_kv_heads % kHeadsPerPass != 0);
+  const int most = (1 << 23) / num_items;
+  p.head_groups = passes <= most ? passes : most > 1 ? most : 1;
+  const dim3 grid((uint32_t)num_items * (uint32_t)p.head_groups);
   if (head_dim == 128)
-    hipLaunchKernelGGL(msa_kv_append_kernel<128>, dim3(num_items), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(msa_kv_append_kernel<128>, grid, dim3(256), 0, s, p);
   else if (head_dim == 64)
-    hipLaunchKernelGGL(msa_kv_append_kernel<64>, dim3(num_items), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(msa_kv_append_kernel<64>, grid, dim3(256), 0, s, p);
   else
     return (int)hipErrorInvalidValue;
   return (int)hipGetLastError();

@@ -63,7 +63,7 @@ RANDOM = [
     # seed, B, Hq, Hkv, d, max_len, max_segs
     (201, 3, 4, 4, 64, 700, 5),
     (202, 4, 32, 8, 128, 1500, 8),
-    (203, 2, 24, 12, 128, 400, 3),   # 12 KV heads: two head passes
+    (203, 2, 24, 12, 128, 400, 3),   # 12 KV heads: six head pairs
     (204, 5, 8, 1, 64, 333, 9),
     (205, 6, 2, 2, 128, 70, 3),      # short sequences, ragged last blocks
     (206, 3, 16, 16, 64, 900, 12),   # many short segments at odd offsets
@@ -156,3 +156,13 @@ def test_append_then_attention(oracle_lib, cfg_or_case):
     ro, rl = oracle_lib.forward(after)
     check_o(bf16_to_f32(o), ro)
     assert float(np.abs(lse.cpu().numpy().astype(np.float64) - rl).max()) <= LSE_ABS
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hkv", [1, 2, 3, 5, 9])
+def test_append_head_counts_bitexact(oracle_lib, hkv, d):
+    """Two heads to a workgroup: one head, an odd last head, several groups."""
+    inst = workloads.make_random(900 + hkv, num_seqs=3, num_q_heads=hkv, num_kv_heads=hkv,
+                                 head_dim=d, max_len=200, max_segs=4)
+    kn, vn = workloads.make_fresh_kv(inst, 950 + hkv)
+    check_bitexact(inst, kn, vn, oracle_lib)
