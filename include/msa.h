@@ -117,9 +117,10 @@ typedef struct msa_plan_opts {
  *     twice the rows) when the plan has full tiles and a long run of key
  *     steps per workgroup slot;
  *   - else 128-row tiles (two workgroups per CU: one's start-up and tail
- *     overlap the other's work).  When such a plan has few short tiles, its
- *     work items hold at most 32 rows each and run as 32-row tiles do (the
- *     plan's tile_rows and workspace slots stay those of 128-row tiles).
+ *     overlap the other's work).  When such a plan has few short tiles and
+ *     q_tile_tokens and kv_split_tokens are 0, its work items hold at most 32
+ *     rows each and run as 32-row tiles do (the plan's tile_rows and workspace
+ *     slots stay those of 128-row tiles).
  * The flags are exclusive.  32-row tiles need Hq / Hkv <= 32, 128-row tiles
  * Hq / Hkv <= 128 (else MSA_ERR_UNSUPPORTED). */
 #define MSA_PLAN_TILE_ROWS_128 4

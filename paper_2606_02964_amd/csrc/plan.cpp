@@ -289,8 +289,12 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
   // (192 tiles at 0.8K keys: 20.0 us, 20.2 us as 768 items; 344 tiles: 24.9
   // and 42 us); nor do long units pay, which tiles cut finer (58 tiles of up
   // to 28.9K keys: 93 us, 195 us as items).
-  if (!forced_width && o.q_tile_tokens == 0 && P.tile_rows == kTileRowsNarrow && G <= kTileRowsDecode &&
-      (int64_t)narrow_units.size() < kCUs) {
+  // Not with a forced split length: it cuts the items far past one per CU (32
+  // tiles at 2K keys, 104 items, pieces of 64 keys: 1016 partials of tiles, 3296
+  // of items, 64 and 208 MiB), and what a caller gets for it, the partials'
+  // memory and whether they fit msa_forward_noalloc, is that of 128-row tiles.
+  if (!forced_width && o.q_tile_tokens == 0 && o.kv_split_tokens == 0 && P.tile_rows == kTileRowsNarrow &&
+      G <= kTileRowsDecode && (int64_t)narrow_units.size() < kCUs) {
     std::vector<Unit> items = make_units(kTileRowsDecode / G);
     if ((int64_t)items.size() < kCUs) {
       int64_t longest = 0, total_steps = 0;

@@ -103,3 +103,21 @@ def test_tile_width_by_steps_and_fill(lens, segs, hq, hkv, d, rows):
     plan = host_plan(msa, inst)
     check_plan(inst, *msa.msa_plan_export(plan), plan.info(), hq // hkv)
     assert plan.info()["tile_rows"] == rows
+
+
+@pytest.mark.parametrize("lens,segs,hq,hkv,d,split", [
+    ([2048], [[(1948, 100)]], 32, 8, 128, 64),
+    ([8192], [[(8064, 128)]], 8, 2, 128, 64),
+    ([512], [[(128, 64), (384, 64)]], 4, 4, 64, 192),
+    ([3001, 60], [[(0, 40), (2950, 51)], [(9, 51)]], 7, 7, 128, 320),
+])
+def test_forced_split_of_few_tiles_keeps_whole_tiles(lens, segs, hq, hkv, d, split):
+    """A forced split length cuts 128-row tiles, not 32-row items of them: the
+    plan and its workspace are those of forced 128-row tiles."""
+    inst = _inst(lens, segs, hq, hkv, d)
+    auto = host_plan(msa, inst, kv_split_tokens=split)
+    forced = host_plan(msa, inst, kv_split_tokens=split, flags=msa.MSA_PLAN_TILE_ROWS_128)
+    check_plan(inst, *msa.msa_plan_export(auto), auto.info(), hq // hkv)
+    assert auto.info() == forced.info()
+    for a, b in zip(msa.msa_plan_export(auto), msa.msa_plan_export(forced)):
+        assert np.array_equal(a, b)
