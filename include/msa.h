@@ -115,7 +115,8 @@ typedef struct msa_plan_opts {
  *     keys and read K and V straight into registers, two workgroups per CU);
  *   - 256-row tiles (one workgroup per CU; each K/V step is loaded once for
  *     twice the rows) when the plan has full tiles and a long run of key
- *     steps per workgroup slot;
+ *     steps per workgroup slot (with q_tile_tokens or kv_split_tokens given:
+ *     many tiles, full or not, and a longer run);
  *   - else 128-row tiles (two workgroups per CU: one's start-up and tail
  *     overlap the other's work).  When such a plan has few short tiles and
  *     q_tile_tokens and kv_split_tokens are 0, its work items hold at most 32

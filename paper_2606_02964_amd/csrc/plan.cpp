@@ -249,12 +249,17 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
           row_steps += st * u.nrows;
           max_rows = std::max<int64_t>(max_rows, (int64_t)u.nrows * G);
         }
-        const bool d64 = s.head_dim == 64;
+        // The width decides which q_tile_tokens are accepted and how much
+        // memory the pieces of a forced split length take, so plans with either
+        // option widen by the 64-wide rule alone, at both head dimensions: a
+        // rule tuned for speed must not move those limits.
+        const bool given = o.q_tile_tokens > 0 || o.kv_split_tokens > 0;
+        const bool late = given || s.head_dim == 64;
         if (!narrow_units.empty() && max_rows <= kTileRowsDecode)
           rows = kTileRowsDecode;
-        else if (steps >= (d64 ? kWideMinStepsPerSlot64 : kWideMinStepsPerSlot) * 2.0 * kCUs &&
-                 row_steps >= kWideMinFill * steps * narrow_tokens &&
-                 (!d64 || (int64_t)narrow_units.size() >= kWideMinTiles64))
+        else if (steps >= (late ? kWideMinStepsPerSlot64 : kWideMinStepsPerSlot) * 2.0 * kCUs &&
+                 (given || row_steps >= kWideMinFill * steps * narrow_tokens) &&
+                 (!late || (int64_t)narrow_units.size() >= kWideMinTiles64))
           rows = kTileRowsWide;
       }
     }

@@ -121,3 +121,27 @@ def test_forced_split_of_few_tiles_keeps_whole_tiles(lens, segs, hq, hkv, d, spl
     assert auto.info() == forced.info()
     for a, b in zip(msa.msa_plan_export(auto), msa.msa_plan_export(forced)):
         assert np.array_equal(a, b)
+
+
+LONG = ([10240], [[(0, 5056), (10112, 128)]], 32, 8, 128)  # 109 key steps per workgroup slot
+MUCH_DECODING = ([16000] * 8 + [12000] * 40, [[(15000, 1000)]] * 8 + [[(11999, 1)]] * 40, 32, 8, 128)
+
+
+@pytest.mark.parametrize("layout,rows", [(LONG, 128), (MUCH_DECODING, 256)])
+@pytest.mark.parametrize("opts", [dict(q_tile_tokens=32), dict(kv_split_tokens=4096),
+                                  dict(q_tile_tokens=20, kv_split_tokens=1024)])
+def test_tile_width_with_given_tokens(layout, rows, opts):
+    """Options whose accepted values or partials depend on the tile width:
+    wide from 1024 tiles and 384 key steps per slot, however full."""
+    inst = _inst(*layout)
+    plan = host_plan(msa, inst, **opts)
+    check_plan(inst, *msa.msa_plan_export(plan), plan.info(), 4)
+    assert plan.info()["tile_rows"] == rows
+
+
+def test_q_tile_tokens_of_wide_tiles():
+    """64 tokens of 4 heads need 256-row tiles."""
+    assert host_plan(msa, _inst(*MUCH_DECODING), q_tile_tokens=64).info()["tile_rows"] == 256
+    with pytest.raises(msa.MsaError) as e:
+        host_plan(msa, _inst(*LONG), q_tile_tokens=64)
+    assert e.value.status == msa.MSA_ERR_INVALID_ARG
