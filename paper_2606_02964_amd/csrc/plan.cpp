@@ -38,7 +38,6 @@
 #include <cmath>
 #include <cstring>
 #include <functional>
-#include <numeric>
 #include <queue>
 #include <utility>
 
@@ -442,9 +441,12 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
   std::vector<std::vector<int32_t>> queue(kXcds);
   std::vector<std::vector<Part>> parts(kXcds);
   auto place = [&](int32_t gi, bool whole) {  // whole: not at all if it does not fit one XCD
-    int by_load[kXcds];
-    std::iota(by_load, by_load + kXcds, 0);
-    std::stable_sort(by_load, by_load + kXcds, [&](int a, int b) { return load[(size_t)a] < load[(size_t)b]; });
+    int by_load[kXcds];  // least loaded first, then lowest (std::stable_sort would allocate on every call)
+    for (int x = 0; x < kXcds; ++x) {
+      int i = x;
+      for (; i > 0 && load[(size_t)x] < load[(size_t)by_load[i - 1]]; --i) by_load[i] = by_load[i - 1];
+      by_load[i] = x;
+    }
     if (whole && load[(size_t)by_load[0]] + gcost[(size_t)gi] > full_small) return false;
     int k = 1;
     if (!whole)
@@ -491,6 +493,7 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
   std::vector<int32_t> unit_count(units.size(), 0);
   for (int x = 0; x < kXcds; ++x) {
     const auto& qx = queue[(size_t)x];
+    if (qx.empty()) continue;
     auto& px = parts[(size_t)x];
     std::stable_sort(px.begin(), px.end(), [&](const Part& a, const Part& b) {
       const double ma = gmax[(size_t)a.group], mb = gmax[(size_t)b.group];
@@ -532,8 +535,8 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
       capacity = std::max(capacity, kMinSplitSteps + ov);
     }
     typedef std::pair<double, int> Slot;  // (load, workgroup of this XCD): least loaded first, then lowest
-    std::priority_queue<Slot, std::vector<Slot>, std::greater<Slot>> slots;
-    for (int i = 0; i < wgs_per_xcd; ++i) slots.push(Slot(0.0, i));
+    std::vector<Slot> slots;  // heap of the workgroups in use; pieces take the idle ones first, in turn
+    slots.reserve((size_t)wgs_per_xcd);
     auto shorter = [&](const Piece& a, const Piece& b) { return a.hi - a.lo < b.hi - b.lo; };
     std::priority_queue<Piece, std::vector<Piece>, decltype(shorter)> tails(shorter);
     for (const Part& part : px) {
@@ -546,8 +549,12 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
           p = tails.top();
           tails.pop();
         }
-        Slot s0 = slots.top();
-        slots.pop();
+        Slot s0(0.0, (int)slots.size());
+        if (s0.second == wgs_per_xcd) {
+          std::pop_heap(slots.begin(), slots.end(), std::greater<Slot>());
+          s0 = slots.back();
+          slots.pop_back();
+        }
         const int64_t n = steps(p.hi - p.lo);
         if (cut_to_fit && cuts_left > 0 && n > kMinSplitSteps && s0.first + (double)n + ov > capacity) {
           --cuts_left;
@@ -561,7 +568,8 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
         pieces.push_back(p);
         ++unit_count[(size_t)p.unit];
         s0.first += pcost(p);
-        slots.push(s0);
+        slots.push_back(s0);
+        std::push_heap(slots.begin(), slots.end(), std::greater<Slot>());
       }
     }
   }
