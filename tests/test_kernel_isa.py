@@ -79,16 +79,17 @@ def test_no_spills_or_scratch(compiled, src):
 
 def test_attention_occupancy(compiled):
     kernels = {k: v for k, v in _resources(compiled["attn.hip"][1]).items()
-               if "msa_attn_kernel" in k or "msa_decode_kernel" in k}
-    # d in {64, 128} x {4, 8 waves, 32-row tiles} x {bf16 weights, precise weights}
-    assert len(kernels) == 12
+               if "msa_attn_kernel" in k or "msa_helped_kernel" in k or "msa_decode_kernel" in k}
+    # d in {64, 128} x {4, 4 + 4 helping, 8 waves, 32-row tiles} x {bf16 weights, precise weights}
+    assert len(kernels) == 16
     for name, r in kernels.items():
         assert r["Occupancy"] >= 2, (name, r)
 
 
 def test_operand_reads_run_ahead(compiled):
     asm, remarks = compiled["attn.hip"]
-    names = [k for k in _resources(remarks) if "msa_attn_kernel" in k]
+    names = [k for k in _resources(remarks) if "msa_attn_kernel" in k or "msa_helped_kernel" in k]
+    assert len(names) == 12
     for name in names:
         body = _body(asm, name)
         waits = re.findall(r"s_waitcnt lgkmcnt\((\d+)\)", body)
