@@ -34,15 +34,16 @@
 //     hi = bf16(w) and lo = bf16(w - hi), with a second PV pass on lo, and
 //     its row sum adds them in fp32: rows whose weight sits on a few keys
 //     then carry their weights to about 2^-18 instead of 2^-9.
-// Steps whose successor needs no mask run software-pipelined in pairs: the
-// QK MFMAs of step j+1 are interleaved with the exponentials of step j, so
-// that each of them is followed by independent vector work.  The diagonal
-// steps and the last one run the same operations without overlap.
+// Steps that need no mask run software-pipelined, in pairs and then up to two
+// singly: the QK MFMAs of step j+1 are interleaved with the exponentials of
+// step j, so that each of them is followed by independent vector work.  The
+// diagonal steps and a wave's last one (with precise weights also the one
+// before a diagonal step) run the same operations without overlap.
 // msa_decode: 32-row tiles of decode-like plans and 32-row items of plans with
-// few short tiles; the four waves of a
-// workgroup split the tile's keys, read K and V straight into registers and
-// merge their softmax states through LDS (see the kernel); masked
-// half-steps carry their weights as hi + lo terms, as above.
+// few short tiles; the four waves of a workgroup split the tile's keys, read K
+// and V straight into registers and merge their softmax states through LDS
+// (see the kernel); the half-steps of a row's diagonal step carry its weights
+// as hi + lo terms, as above.
 // Both kernels also come in a precise-weights form (kPrecise, selected by
 // the plan): every step, or half-step, carries every row's weights as
 // hi + lo terms.
@@ -430,7 +431,9 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
     }
   };
 
-  // One step j, scores of step j in sbuf[B]; neither it nor step j+1 is masked:
+  // One step j < nw - 1 that needs no mask, its scores in sbuf[B].  Step j+1
+  // may need one (not with precise weights, which take its row max here): its
+  // scores leave unmasked and the caller masks them.
   //   block 1: QK of step j+1 into sbuf[1-B], interleaved with the weights of
   //            step j; then settle the weights of step j (rarely does work)
   //   block 2: PV of step j, with the page addresses of the next copies
@@ -571,12 +574,13 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const WorkItem w,
   }
   lds_barrier();  // every wave is done with K_0 before K_2 replaces it
 
-  // Iterations run in two loops.  The first handles two steps per trip
+  // Iterations run in three parts.  The first handles two steps per trip
   // while both steps and their successors need no mask (the scores of step j
   // alternate between sbuf[0] and sbuf[1], so a trip starts and ends with
-  // them in sbuf[0]).  The second handles the diagonal steps and the last one
-  // at a time, copying the next scores back to sbuf[0].  Waves may split their
-  // steps differently between the loops; every step still ends with exactly
+  // them in sbuf[0]).  The second pipelines the one or two steps without a
+  // mask that may remain.  The third handles the diagonal steps and the last
+  // one at a time, with every step's scores in sbuf[0].  Waves may split their
+  // steps differently between the parts; every step still ends with exactly
   // one barrier.
   auto tail = [&]() {
     wait_dma<0>();

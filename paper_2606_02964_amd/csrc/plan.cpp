@@ -19,8 +19,10 @@
 //      split the tile's keys).  A 128-row plan of few short tiles runs as
 //      items of up to 32 rows, in the same way;
 //   3. units: tile x KV head, keys [0, max position in tile + 1);
-//   4. key splits of 32-row plans: the cut length is the shortest whose
-//      pieces all fit one round of the workgroup slots; other plans cut
+//   4. key splits of 32-row tiles and items: the cut length is the shortest
+//      whose pieces all fit one round of the workgroup slots, or, below 1024
+//      keys, whose pieces (of 256 keys or more) have a CU each; units are left
+//      whole where cutting gains less than a merge takes.  Other plans cut
 //      units in step 6.  Split units are merged later by log-sum-exp;
 //   5. order: (sequence, KV head) groups keep to one of the 8 XCDs (blockIdx
 //      i runs on XCD i % 8) so tiles sharing K/V share one XCD's L2; groups
@@ -362,11 +364,19 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
       whole_keys = kWholeKeysDecode;
       split_keys = shortest_cut(units, kMinSplitKeysDecode, whole_keys, kCUs);
       if (P.tile_rows == kTileRowsDecode) split_keys = std::min(split_keys, kMinSplitKeys);
-      int64_t longest = 0;
-      for (const Unit& u : units) longest = std::max<int64_t>(longest, u.kv_hi);
+      int64_t longest = 0, kept = 0;  // of all units, of those that stay whole
+      for (const Unit& u : units) {
+        longest = std::max<int64_t>(longest, u.kv_hi);
+        if (u.kv_hi <= whole_keys) kept = std::max<int64_t>(kept, u.kv_hi);
+      }
       // (a merge launch takes as long as a chain of 500 keys: 216 items of up to
-      // 1.7K keys 13.8 us in pieces of up to 1408, 12.9 whole)
-      if (longest - split_keys < 2 * kMinSplitKeysDecode) split_keys = 0;
+      // 1.7K keys 13.8 us in pieces of up to 1408, 12.9 whole.  Decode rows of up
+      // to 1024 keys are cut only if the rows that stay whole are that much
+      // shorter too: 64 items at d = 64, 9 of them 1024 keys long, take 8.7 us
+      // whole and 9.5 cut beside rows of 650 keys, 8.7 and 7.7 beside 300.)
+      int64_t rest = split_keys;
+      if (P.tile_rows == kTileRowsDecode && longest <= kMinSplitKeys) rest = std::max(rest, kept);
+      if (longest - rest < 2 * kMinSplitKeysDecode) split_keys = 0;
     }
   }
   // A chunk is a run of key steps of one unit that is handed to workgroups

@@ -14,7 +14,7 @@ Each case draws its own shape and plan options:
 
 The bar is the same as the other parity tests: plain max-abs <= 1e-2 where
 the oracle's value is below 4 in magnitude (see ``tolerance.py`` for the
-reading above that), mean-abs <= 1e-3, lse within 2^-9 + 1e-4.
+reading above that), mean-abs <= 1e-3, lse within 2.5e-4.
 """
 import numpy as np
 import pytest

@@ -145,3 +145,19 @@ def test_q_tile_tokens_of_wide_tiles():
     with pytest.raises(msa.MsaError) as e:
         host_plan(msa, _inst(*LONG), q_tile_tokens=64)
     assert e.value.status == msa.MSA_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("lens,merges", [
+    ([786, 779] + [720] * 8, False),   # cutting 786 keys leaves the 720
+    ([1024] * 2 + [513] * 6, False),
+    ([1024] * 2 + [512] * 6, True),
+    ([1000] * 4, True),
+    ([1100] + [700] * 8, True),        # rows past 1024 keys
+])
+def test_decode_rows_are_cut_only_if_the_longest_chain_falls(lens, merges):
+    """Rows of up to 1024 keys: cut only where the longest item left is 512
+    keys shorter, which is what the merge launch costs."""
+    inst = _inst(lens, [[(n - 1, 1)] for n in lens], 28, 4, 128)
+    plan = host_plan(msa, inst)
+    check_plan(inst, *msa.msa_plan_export(plan), plan.info(), 7)
+    assert plan.info()["tile_rows"] == 32 and (plan.info()["num_merge"] > 0) == merges
