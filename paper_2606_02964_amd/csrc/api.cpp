@@ -342,6 +342,7 @@ msa_status msa_kv_append(msa_plan_t plan, const void* k_new, const void* v_new,
   p.num_kv_heads = s.num_kv_heads;
   p.max_blocks = s.max_blocks_per_seq;
   p.num_blocks = s.num_blocks;
+  p.total_q = (int32_t)hp.total_q;
   const int rc = msa::launch_kv_append(p, s.head_dim, (int)hp.append.size(), hip_stream);
   if (rc != 0)
     return set_error(MSA_ERR_DEVICE, std::string("msa_kv_append: launch failed: ") +

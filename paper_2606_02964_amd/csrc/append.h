@@ -34,6 +34,7 @@ struct AppendParams {
   int32_t num_kv_heads;
   int32_t max_blocks;
   int32_t num_blocks;
+  int32_t total_q;      // rows of all slices (launch_kv_append's choice of kernel)
   int32_t head_groups;  // workgroups that share a slice's heads (set by launch_kv_append)
 };
 

@@ -1,9 +1,9 @@
 // append.hip -- gfx950 kernel that writes the fresh K/V of the packed query
 // rows into their paged cache slots.
 //
-// One workgroup (256 threads) takes two KV heads of one slice: the n <= 16
-// consecutive rows of one segment that land in one cache block (the planner
-// cuts every segment at block boundaries):
+// One workgroup (256 threads) takes two KV heads, or all of them, of one slice:
+// the n <= 16 consecutive rows of one segment that land in one cache block (the
+// planner cuts every segment at block boundaries):
 //   * K blocks are token-major, so each (row, head) is one contiguous d-vector
 //     in both the source and the cache: 16-byte loads and stores, 16 lanes per
 //     row (256 contiguous bytes for d = 128).
@@ -15,14 +15,16 @@
 //     consecutive tokens of one channel.
 // A slice whose block-table entry is outside [0, num_blocks) is not written.
 // The kernel is bound by HBM: it reads and writes each fresh K/V byte once.
-// A slice's heads are spread over workgroups because one workgroup of all 8
+// A full slice's heads are spread over workgroups because one workgroup of all 8
 // heads runs its reads, its LDS transpose and its stores one after the other,
 // in 35 KB of LDS that leave room for four per CU (20480 rows, 8 heads, d = 128:
 // 1280 workgroups for 1024 places).  168 MB in 40.1 us with 8 heads a
 // workgroup, 37.8 with 4, 35.6 with 2 (4.7 TB/s; a device copy reaches 4.9),
 // 34.6 with 1; 128 decode rows with their attention 299.4, 299.3, 298.9 and
 // 300.0 us, hence 2.  (Issuing all of a thread's loads before its stores,
-// with two lanes to a V channel, took 49 us at 2 heads.)
+// with two lanes to a V channel, took 49 us at 2 heads.)  Where two heads of a
+// slice are too little work for a workgroup it takes the whole slice, eight
+// heads at a time; launch_kv_append has the rule.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -32,9 +34,7 @@
 namespace msa {
 namespace {
 
-constexpr int kHeadsPerPass = 2;  // KV heads a workgroup takes at a time
-
-template <int D>
+template <int D, int kHeadsPerPass>  // KV heads a workgroup takes at a time
 __global__ __launch_bounds__(256) void msa_kv_append_kernel(AppendParams p) {
   constexpr int kChunks = D / 8;  // 16-byte chunks of one head vector
   constexpr int kPitch = D + 8;   // LDS row pitch (elements), breaks bank aliasing
@@ -104,23 +104,44 @@ __global__ __launch_bounds__(256) void msa_kv_append_kernel(AppendParams p) {
 
 }  // namespace
 
-int launch_kv_append(const AppendParams& params, int head_dim, int num_items, void* stream) {
+namespace {
+
+template <int D>
+int launch_heads(AppendParams p, bool whole_slices, int num_items, hipStream_t s) {
+  // a workgroup per (slice, two heads); fewer, each looping over its heads,
+  // where the grid would pass 2^23 workgroups
+  const int passes = p.num_kv_heads / 2 + p.num_kv_heads % 2;
+  const int most = (1 << 23) / num_items;
+  p.head_groups = whole_slices || most < 1 ? 1 : passes <= most ? passes : most;
+  const dim3 grid((uint32_t)num_items * (uint32_t)p.head_groups);
+  if (whole_slices)
+    hipLaunchKernelGGL((msa_kv_append_kernel<D, 8>), grid, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((msa_kv_append_kernel<D, 2>), grid, dim3(256), 0, s, p);
+  return (int)hipGetLastError();
+}
+
+}  // namespace
+
+int launch_kv_append(const AppendParams& p, int head_dim, int num_items, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (num_items <= 0) return 0;
-  AppendParams p = params;
-  // a workgroup per (slice, heads of a pass); fewer, each looping over its
-  // heads, where the grid would pass 2^23 workgroups
-  const int passes = p.num_kv_heads / kHeadsPerPass + (p.num_kv_heads % kHeadsPerPass != 0);
-  const int most = (1 << 23) / num_items;
-  p.head_groups = passes <= most ? passes : most > 1 ? most : 1;
-  const dim3 grid((uint32_t)num_items * (uint32_t)p.head_groups);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(msa_kv_append_kernel<128>, grid, dim3(256), 0, s, p);
-  else if (head_dim == 64)
-    hipLaunchKernelGGL(msa_kv_append_kernel<64>, grid, dim3(256), 0, s, p);
-  else
-    return (int)hipErrorInvalidValue;
-  return (int)hipGetLastError();
+  // One workgroup a slice, taking its heads eight at a time,
+  // - where slices are short, since a workgroup's fixed cost outweighs two heads
+  //   of a few rows.  The line is at 640 channels of a head, 5 rows at d = 128,
+  //   10 at d = 64 (2048 slices, 8 heads, in groups of two / whole: d = 128, 1
+  //   row 34.6 / 33.5 us, 4 rows 40.7 / 40.3, 6 rows 46.4 / 47.7; d = 64, 1 row
+  //   20.8 / 15.6, 8 rows 25.4 / 24.5, 16 rows 27.7 / 29.7);
+  // - where all heads are up to 320 channels (16384 rows, d = 64: 4 heads 9.4 /
+  //   9.2 us), or an odd number of heads up to 448, whose last workgroup would
+  //   hold one (d = 128, 3 heads 14.5 / 13.8; d = 64, 3 heads 8.6 / 7.2, 5 heads
+  //   11.6 / 11.5; 6 heads stay in twos: 2048 full slices 21.9 / 24.3).
+  const int64_t channels = (int64_t)p.num_kv_heads * head_dim;
+  const bool whole = (int64_t)p.total_q * head_dim < (int64_t)640 * num_items || channels <= 320 ||
+                     (channels <= 448 && p.num_kv_heads % 2 != 0);
+  if (head_dim == 128) return launch_heads<128>(p, whole, num_items, s);
+  if (head_dim == 64) return launch_heads<64>(p, whole, num_items, s);
+  return (int)hipErrorInvalidValue;
 }
 
 }  // namespace msa

@@ -63,7 +63,7 @@ RANDOM = [
     # seed, B, Hq, Hkv, d, max_len, max_segs
     (201, 3, 4, 4, 64, 700, 5),
     (202, 4, 32, 8, 128, 1500, 8),
-    (203, 2, 24, 12, 128, 400, 3),   # 12 KV heads: six head pairs
+    (203, 2, 24, 12, 128, 400, 3),   # 12 KV heads
     (204, 5, 8, 1, 64, 333, 9),
     (205, 6, 2, 2, 128, 70, 3),      # short sequences, ragged last blocks
     (206, 3, 16, 16, 64, 900, 12),   # many short segments at odd offsets
@@ -161,8 +161,20 @@ def test_append_then_attention(oracle_lib, cfg_or_case):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("hkv", [1, 2, 3, 5, 9])
 def test_append_head_counts_bitexact(oracle_lib, hkv, d):
-    """Two heads to a workgroup: one head, an odd last head, several groups."""
+    """One head, an odd last head, several groups of heads."""
     inst = workloads.make_random(900 + hkv, num_seqs=3, num_q_heads=hkv, num_kv_heads=hkv,
                                  head_dim=d, max_len=200, max_segs=4)
     kn, vn = workloads.make_fresh_kv(inst, 950 + hkv)
+    check_bitexact(inst, kn, vn, oracle_lib)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hkv", [1, 3, 4, 5, 6, 7, 8, 9, 17])
+@pytest.mark.parametrize("n", [1, 4, 5, 9, 10, 16])
+def test_append_slice_lengths_bitexact(oracle_lib, n, hkv, d):
+    """Slices of n rows, at a block's start and inside it: two heads to a
+    workgroup or whole slices, with whole and partial last groups of heads."""
+    segs = [(0, n), (32, n), (67, n), (130, min(n, 14))]
+    inst = workloads.make_layout(970 + n, [200, 70], [segs, [(48, n)]], hkv, hkv, d, keep_logical=False)
+    kn, vn = workloads.make_fresh_kv(inst, 980 + hkv)
     check_bitexact(inst, kn, vn, oracle_lib)
