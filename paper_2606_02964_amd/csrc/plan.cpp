@@ -250,6 +250,10 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
           row_steps += st * u.nrows;
           max_rows = std::max<int64_t>(max_rows, (int64_t)u.nrows * G);
         }
+        // Units that are never cut take as long as the longest chain, and up to
+        // one narrow unit per CU, a narrow step is the shorter (30K keys, d = 128:
+        // 120 narrow units 365 us, 60 wide ones 596; past that, narrow units share
+        // CUs: 264 narrow 615, 132 wide 611, 476 and 238 762 / 742).
         // The width decides which q_tile_tokens are accepted and how much
         // memory the pieces of a forced split length take, so plans with either
         // option widen by the 64-wide rule alone, at both head dimensions: a
@@ -260,7 +264,8 @@ msa_status build_plan(const msa_shape* shape, const int32_t* seq_kv_len, const i
           rows = kTileRowsDecode;
         else if (steps >= (late ? kWideMinStepsPerSlot64 : kWideMinStepsPerSlot) * 2.0 * kCUs &&
                  (given || row_steps >= kWideMinFill * steps * narrow_tokens) &&
-                 (!late || (int64_t)narrow_units.size() >= kWideMinTiles64))
+                 (!late || (int64_t)narrow_units.size() >= kWideMinTiles64) &&
+                 (!(o.flags & MSA_PLAN_NO_AUTO_SPLIT) || (int64_t)narrow_units.size() > kCUs))
           rows = kTileRowsWide;
       }
     }

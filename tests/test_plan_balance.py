@@ -161,3 +161,16 @@ def test_decode_rows_are_cut_only_if_the_longest_chain_falls(lens, merges):
     plan = host_plan(msa, inst)
     check_plan(inst, *msa.msa_plan_export(plan), plan.info(), 7)
     assert plan.info()["tile_rows"] == 32 and (plan.info()["num_merge"] > 0) == merges
+
+
+@pytest.mark.parametrize("new,hq,hkv,flags,rows", [
+    (1900, 8, 2, 0, 256),
+    (1900, 8, 2, msa.MSA_PLAN_NO_AUTO_SPLIT, 128),   # 120 narrow units
+    (3600, 8, 2, msa.MSA_PLAN_NO_AUTO_SPLIT, 128),   # 226
+    (3600, 16, 2, msa.MSA_PLAN_NO_AUTO_SPLIT, 256),  # 450
+])
+def test_uncut_units_widen_past_one_per_cu(new, hq, hkv, flags, rows):
+    inst = _inst([30000], [[(30000 - new, new)]], hq, hkv, 128)
+    plan = host_plan(msa, inst, flags=flags)
+    check_plan(inst, *msa.msa_plan_export(plan), plan.info(), hq // hkv)
+    assert plan.info()["tile_rows"] == rows
