@@ -1,24 +1,26 @@
 // msa_internal.h -- tables shared by the host planner and the gfx950 kernels.
 //
-// A work item is one tile: up to tile_rows query rows of one sequence
-// that share one KV head (tokens x the G = Hq/Hkv query heads of the group,
-// row r <-> token r / G, head r % G) and one contiguous key range.  The
-// launch is persistent: each workgroup runs its own list of items.  The
-// planner packs consecutive query tokens of a sequence into a tile even
-// across segment gaps; each row keeps its own causal limit (its absolute
-// position), which is what the paper's per-token "equivalent seq_len" array
-// provides (Sec. 4.1).
+// A work item is up to tile_rows query rows of one sequence (one tile, or up
+// to 32 rows of one in plans with few short tiles) that share one KV head
+// (tokens x the G = Hq/Hkv query heads of the group, row r <-> token r / G,
+// head r % G) and one contiguous key range.  The launch is persistent: each
+// workgroup runs its own list of items.  The planner packs consecutive query
+// tokens of a sequence into a tile even across segment gaps; each row keeps
+// its own causal limit (its absolute position), which is what the paper's
+// per-token "equivalent seq_len" array provides (Sec. 4.1).
 #pragma once
 
 #include <cstdint>
 
 namespace msa {
 
-// Tile widths: 128 rows (4 waves x 32 rows, two workgroups per CU) for
-// small plans, 256 rows (8 waves, one workgroup per CU) for plans with many
-// tiles (a wider tile loads each K/V step once for twice the rows), and 32
-// rows for decode-like plans (every tile holds at most 32 rows; the four
-// waves split the tile's keys and read K/V straight into registers).
+// Tile widths: 128 rows (4 waves x 32 rows, two workgroups per CU, or one with
+// 4 more waves that copy) for small plans, 256 rows (8 waves, one workgroup per
+// CU) for plans with full tiles and a long run of key steps (a wider tile loads
+// each K/V step once for twice the rows), and 32 rows for decode-like plans
+// (every tile holds at most 32 rows; the four waves split the tile's keys and
+// read K/V straight into registers), which also run the items of up to 32 rows
+// of plans with few short 128-row tiles.
 constexpr int kTileRowsNarrow = 128;
 constexpr int kTileRowsWide = 256;
 constexpr int kTileRowsDecode = 32;
